@@ -52,6 +52,9 @@ struct GemmDesc {
   // path then copies the column strip like an operand tile
   const uint16_t* Aci = nullptr; int64_t ldaci = 0;
   float* Cc = nullptr; int64_t ldcc = 0, sCc0 = 0, sCc1 = 0;
+  // optional bf16 image of the stored Cc (four rows per checksum block as in
+  // Aci), for the GEMM that takes it as its strip
+  uint16_t* Cci = nullptr; int64_t ldcci = 0, sCci0 = 0, sCci1 = 0;
   int Rm = 128;
 
   const float* Br = nullptr; int64_t ldbr = 0, sBr0 = 0, sBr1 = 0;
@@ -59,6 +62,9 @@ struct GemmDesc {
   // rows per checksum block along k, ldbri elements each)
   const uint16_t* Bri = nullptr; int64_t ldbri = 0;
   float* Cr = nullptr; int64_t ldcr = 0, sCr0 = 0, sCr1 = 0;
+  // optional bf16 image of the stored Cr, transposed: per checksum block
+  // four rows (c1 hi, c1 lo, c2 hi, c2 lo) along m, each ldcri elements long
+  uint16_t* Cri = nullptr; int64_t ldcri = 0, sCri0 = 0, sCri1 = 0;
   int Rn = 128;
   int cr_n_begin = 0;
 
@@ -94,11 +100,16 @@ enum class Tile : int { T128x128 = 1, T128x64 = 2, T128x128S1 = 3 };
 hipError_t launch_gemm(const GemmDesc& g, int dtype, bool c_fp32, Layout la, Layout lb,
                        Tile tile, hipStream_t stream);
 
+// The wide-tile form of launch_gemm (gemm_wide.hip): unbatched bf16 products
+// on the direct path with their checksum strips from bf16 images;
+// hipErrorNotSupported for any other (nothing launched).
+hipError_t launch_gemm_wide(const GemmDesc& g, bool c_fp32, Layout la, Layout lb,
+                            hipStream_t stream);
+
 // A weight gradient w (MN-major operands, fp32 output, whole or as its K
 // slices, as launch_gemm takes it) and a projection p (K-major operands,
-// bf16 output, 128 x 128 tiles) in one launch, when both take the direct
-// path and w's workgroups are a multiple of 8; hipErrorNotSupported when
-// they do not qualify (nothing launched: launch them one by one).
+// bf16 output) in one launch of wide tiles; hipErrorNotSupported when they
+// do not qualify (nothing launched: launch them one by one).
 hipError_t launch_gemm_pair(const GemmDesc& w, const GemmDesc& p, int dtype,
                             hipStream_t stream);
 

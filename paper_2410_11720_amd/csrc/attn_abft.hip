@@ -51,9 +51,10 @@ struct Layout_ {
   // that take them as column strips copy them like operand tiles
   size_t xci, doci, dqkvci;
   size_t xri;  // bf16 image of X^r, transposed ([nh][4][T]): dW^QKV's strip
-  size_t clri; // the same of CL^r, written by the fused forward: dW^O's strip
+  size_t clri; // the same of CL^r, written by the fused forward or the context
+               // GEMM: dW^O's strip
   size_t wvri; // the same of W^V r ([nh][4][H]): the QKV GEMM's row strip
-  size_t clci; // bf16 image of CL^c (fused form): the output projection's strip
+  size_t clci; // bf16 image of CL^c: the output projection's strip
   size_t skp, skc;  // split-K partials of the weight gradients and their checksums
   size_t stats;     // fused forward: softmax max and sum per query [B][nh][S][2]
   size_t drow;      // fused backward: D = dCL . CL per query [B][nh][S]
@@ -135,6 +136,7 @@ Layout_ make_layout(const Dims& d) {
   const size_t c2 = ks2 > 1 ? size_t(ks2) * 2 * d.nh * d.H : 0;
   L.skp = take((p1 > p2 ? p1 : p2) * f);
   L.skc = take((c1 > c2 ? c1 : c2) * f);
+  L.clri = take(size_t(d.nh) * 4 * d.T * 2);
   L.total = off;
   return L;
 }
@@ -567,10 +569,18 @@ int forward_impl(const attn_abft_config* cfg, const Dims& d, const Layout_& L, c
     if (need_apc) {
       g.Ac = F(L.apc); g.ldac = S; g.sAc0 = nh * nq * 2 * S; g.sAc1 = nq * 2 * S; g.Rm = int(R);
       g.Cc = F(L.clc); g.ldcc = H; g.sCc0 = nq * 2 * H; g.sCc1 = hd;
+      if (es == 2) {
+        g.Cci = reinterpret_cast<uint16_t*>(ws + L.clci);
+        g.ldcci = H; g.sCci0 = nq * 4 * H; g.sCci1 = hd;
+      }
     }
     if (need_vr) {
       g.Br = F(L.vr); g.ldbr = 2 * nh; g.sBr0 = S * 2 * nh; g.sBr1 = 2; g.Rn = int(hd);
       g.Cr = F(L.clr); g.ldcr = 2 * nh; g.sCr0 = S * 2 * nh; g.sCr1 = 2;
+      if (es == 2) {
+        g.Cri = reinterpret_cast<uint16_t*>(ws + L.clri);
+        g.ldcri = T; g.sCri0 = S; g.sCri1 = 4 * T;
+      }
     }
     if (p.sec_cl) g.verify = 2;
     g.causal = cfg->causal ? 2 : 0;
@@ -587,7 +597,7 @@ int forward_impl(const attn_abft_config* cfg, const Dims& d, const Layout_& L, c
     g.C = O; g.ldc = H;
     if (p.sec_o) {
       g.Ac = F(L.clc); g.ldac = H; g.Rm = int(R);
-      if (fused && es == 2) {  // the image the fused forward wrote with CL^c
+      if (es == 2) {  // the image written with CL^c
         g.Aci = reinterpret_cast<const uint16_t*>(ws + L.clci); g.ldaci = H;
       }
       g.verify = 1;
@@ -687,7 +697,7 @@ int attn_abft_backward_stages(const attn_abft_config* cfg, const void* dO, const
     g.C = dWo; g.ldc = H;
     if (pb) {
       g.Ac = F(L.clr); g.ldac = 2 * nh; g.Rm = int(hd);
-      if (fused && es == 2) {  // the image the fused forward wrote with CL^r
+      if (es == 2) {  // the image the forward wrote with CL^r
         g.Aci = reinterpret_cast<const uint16_t*>(ws + L.clri); g.ldaci = T;
       }
       g.verify = 1;
@@ -756,6 +766,10 @@ int attn_abft_backward_stages(const attn_abft_config* cfg, const void* dO, const
       g.Ac = F(L.apr); g.ldac = nq * 2; g.sAc0 = nh * S * nq * 2; g.sAc1 = S * nq * 2;
       g.Rm = int(R);
       g.Cc = F(L.dqkvc) + 2 * H; g.ldcc = 3 * H; g.sCc0 = nq * 2 * 3 * H; g.sCc1 = hd;
+      if (es == 2) {
+        g.Cci = reinterpret_cast<uint16_t*>(ws + L.dqkvci) + 2 * H;
+        g.ldcci = 3 * H; g.sCci0 = nq * 4 * 3 * H; g.sCci1 = hd;
+      }
       g.verify = 1;
     }
     g.causal = cfg->causal ? 3 : 0;
@@ -784,6 +798,10 @@ int attn_abft_backward_stages(const attn_abft_config* cfg, const void* dO, const
     if (pb) {
       g.Ac = F(L.dasc); g.ldac = S; g.sAc0 = nh * nq * 2 * S; g.sAc1 = nq * 2 * S; g.Rm = int(R);
       g.Cc = F(L.dqkvc); g.ldcc = 3 * H; g.sCc0 = nq * 2 * 3 * H; g.sCc1 = hd;
+      if (es == 2) {
+        g.Cci = reinterpret_cast<uint16_t*>(ws + L.dqkvci);
+        g.ldcci = 3 * H; g.sCci0 = nq * 4 * 3 * H; g.sCci1 = hd;
+      }
       g.verify = 1;
     }
     g.causal = cfg->causal ? 2 : 0;
@@ -802,6 +820,10 @@ int attn_abft_backward_stages(const attn_abft_config* cfg, const void* dO, const
       g.Ac = F(L.dasr); g.ldac = nq * 2; g.sAc0 = nh * S * nq * 2; g.sAc1 = S * nq * 2;
       g.Rm = int(R);
       g.Cc = F(L.dqkvc) + H; g.ldcc = 3 * H; g.sCc0 = nq * 2 * 3 * H; g.sCc1 = hd;
+      if (es == 2) {
+        g.Cci = reinterpret_cast<uint16_t*>(ws + L.dqkvci) + H;
+        g.ldcci = 3 * H; g.sCci0 = nq * 4 * 3 * H; g.sCci1 = hd;
+      }
       g.verify = 1;
     }
     g.causal = cfg->causal ? 3 : 0;
@@ -844,7 +866,7 @@ int attn_abft_backward_stages(const attn_abft_config* cfg, const void* dO, const
     g.C = dX; g.ldc = H;
     if (pb) {
       g.Ac = F(L.dqkvc); g.ldac = 3 * H; g.Rm = int(R);
-      if (fused && es == 2) {  // the image the encode above wrote
+      if (es == 2) {  // the image written with dQKV^c
         g.Aci = reinterpret_cast<const uint16_t*>(ws + L.dqkvci); g.ldaci = 3 * H;
       }
       g.verify = 1;

@@ -268,6 +268,34 @@ __device__ __forceinline__ bool fault_target(const CoordMap& mp, int N, const ab
   return true;
 }
 
+// A stored checksum pair as four bf16 rows (hi/lo of each) at p, p + ld, ..
+__device__ __forceinline__ void store_image(uint16_t* p, int64_t ld, float c1, float c2) {
+  const bf16_t h1 = f2bf(c1), h2 = f2bf(c2);
+  p[0] = h1;
+  p[ld] = f2bf(c1 - bf2f(h1));
+  p[2 * ld] = h2;
+  p[3 * ld] = f2bf(c2 - bf2f(h2));
+}
+
+// Propagated checksums of the output, with their images: column block `blk`
+// of column n; row block q of row m (z = (b0, b1)).
+__device__ __forceinline__ void store_cc(const GemmDesc& g, int b0, int b1, int64_t kofs, int blk,
+                                         int n, float c1, float c2) {
+  float* Cc = g.Cc + b0 * g.sCc0 + b1 * g.sCc1 + kofs + int64_t(2 * blk) * g.ldcc + n;
+  Cc[0] = c1;
+  Cc[g.ldcc] = c2;
+  if (g.Cci != nullptr)
+    store_image(g.Cci + b0 * g.sCci0 + b1 * g.sCci1 + int64_t(4 * blk) * g.ldcci + n, g.ldcci, c1, c2);
+}
+__device__ __forceinline__ void store_cr(const GemmDesc& g, int b0, int b1, int m, int q, float c1,
+                                         float c2) {
+  float* Cr = g.Cr + b0 * g.sCr0 + b1 * g.sCr1 + int64_t(m) * g.ldcr + 2 * q;
+  Cr[0] = c1;
+  Cr[1] = c2;
+  if (g.Cri != nullptr)
+    store_image(g.Cri + b0 * g.sCri0 + b1 * g.sCri1 + int64_t(4 * q) * g.ldcri + m, g.ldcri, c1, c2);
+}
+
 template <class T, class TC, bool AK, bool BKM>
 __device__ float recompute_elem(const GemmDesc& g, const T* A, const T* B, int m, int n, int k_lo,
                                 int k_hi) {
@@ -1090,23 +1118,18 @@ struct Gemm {
 
     // propagated checksums for the consumers downstream
     if (PROT && cc && g.Cc != nullptr) {
-      float* Cc = g.Cc + b0 * g.sCc0 + b1 * g.sCc1 + int64_t(kslice) * g.sCck;
       for (int v = tid; v < ncb * BN; v += NT) {
         const int blk = v / BN, n = v % BN;
-        if (m0 + blk * g.Rm < g.M && n0 + n < g.N) {
-          Cc[int64_t(rc0 + 2 * blk) * g.ldcc + n0 + n] = ccv[v * 2];
-          Cc[int64_t(rc0 + 2 * blk + 1) * g.ldcc + n0 + n] = ccv[v * 2 + 1];
-        }
+        if (m0 + blk * g.Rm < g.M && n0 + n < g.N)
+          store_cc(g, b0, b1, int64_t(kslice) * g.sCck, rc0 / 2 + blk, n0 + n, ccv[v * 2],
+                   ccv[v * 2 + 1]);
       }
     }
     if (PROT && cr && g.Cr != nullptr) {
-      float* Cr = g.Cr + b0 * g.sCr0 + b1 * g.sCr1;
       for (int u = tid; u < BM * nrb; u += NT) {
         const int row = u / nrb, rb = u % nrb;
-        if (m0 + row < g.M && n0 + rb * g.Rn < g.N) {
-          Cr[int64_t(m0 + row) * g.ldcr + qc0 + 2 * rb] = rcv[u * 2];
-          Cr[int64_t(m0 + row) * g.ldcr + qc0 + 2 * rb + 1] = rcv[u * 2 + 1];
-        }
+        if (m0 + row < g.M && n0 + rb * g.Rn < g.N)
+          store_cr(g, b0, b1, m0 + row, qc0 / 2 + rb, rcv[u * 2], rcv[u * 2 + 1]);
       }
     }
     }  // epilogue
@@ -1228,27 +1251,21 @@ struct Gemm {
     // propagated checksums for the consumers downstream (a correction
     // changes the output, not its propagated checksums)
     if (cc && g.Cc != nullptr && own_c) {
-      float* Cc = g.Cc + b0 * g.sCc0 + b1 * g.sCc1;
 #pragma unroll
       for (int j = 0; j < JN; ++j) {
         const int n = n0 + wn * WN + j * 16 + fr;
-        if (n < g.N) {
-          Cc[int64_t(rc0 + 2 * g4) * g.ldcc + n] = accs[j][0] + accs[j][1];
-          Cc[int64_t(rc0 + 2 * g4 + 1) * g.ldcc + n] = accs[j][2] + accs[j][3];
-        }
+        if (n < g.N)
+          store_cc(g, b0, b1, 0, rc0 / 2 + g4, n, accs[j][0] + accs[j][1], accs[j][2] + accs[j][3]);
       }
     }
     if (cr && g.Cr != nullptr) {
       const int nrb = BN >> __builtin_ctz(g.Rn);
       if (g4 < nrb && n0 + g4 * g.Rn < g.N) {
-        float* Cr = g.Cr + b0 * g.sCr0 + b1 * g.sCr1;
 #pragma unroll
         for (int i = 0; i < IS; ++i) {
           const int m = m0 + (IS * wn + i) * 16 + fr;
-          if (m < g.M) {
-            Cr[int64_t(m) * g.ldcr + qc0 + 2 * g4] = accr[i][0] + accr[i][1];
-            Cr[int64_t(m) * g.ldcr + qc0 + 2 * g4 + 1] = accr[i][2] + accr[i][3];
-          }
+          if (m < g.M)
+            store_cr(g, b0, b1, m, qc0 / 2 + g4, accr[i][0] + accr[i][1], accr[i][2] + accr[i][3]);
         }
       }
     }
@@ -1339,23 +1356,17 @@ struct Gemm {
     }
     if (nrb > 0) {  // checksums the passes refreshed (1R / 1C) go downstream
       if (cc && g.Cc != nullptr) {
-        float* Cc = g.Cc + b0 * g.sCc0 + b1 * g.sCc1;
         for (int v = tid; v < ncb * BN; v += NT) {
           const int blk = v / BN, n = v % BN;
-          if (m0 + blk * g.Rm < g.M && n0 + n < g.N) {
-            Cc[int64_t(rc0 + 2 * blk) * g.ldcc + n0 + n] = ccv[v * 2];
-            Cc[int64_t(rc0 + 2 * blk + 1) * g.ldcc + n0 + n] = ccv[v * 2 + 1];
-          }
+          if (m0 + blk * g.Rm < g.M && n0 + n < g.N)
+            store_cc(g, b0, b1, 0, rc0 / 2 + blk, n0 + n, ccv[v * 2], ccv[v * 2 + 1]);
         }
       }
       if (g.Cr != nullptr) {
-        float* Cr = g.Cr + b0 * g.sCr0 + b1 * g.sCr1;
         for (int u = tid; u < BM * nrb; u += NT) {
           const int row = u / nrb, rb = u % nrb;
-          if (m0 + row < g.M && n0 + rb * g.Rn < g.N) {
-            Cr[int64_t(m0 + row) * g.ldcr + qc0 + 2 * rb] = rcv[u * 2];
-            Cr[int64_t(m0 + row) * g.ldcr + qc0 + 2 * rb + 1] = rcv[u * 2 + 1];
-          }
+          if (m0 + row < g.M && n0 + rb * g.Rn < g.N)
+            store_cr(g, b0, b1, m0 + row, qc0 / 2 + rb, rcv[u * 2], rcv[u * 2 + 1]);
         }
       }
     }
@@ -1618,59 +1629,6 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Two independent GEMMs of the layer's backward in one launch: workgroups
-// [0, n1) run a weight gradient (MN-major operands, fp32 output, whole or
-// in K slices: the longer work items first), the rest a projection with
-// K-major operands and bf16 output; both 128 x 128 tiles on the direct
-// path. Alone, each leaves CUs idle in its last round of workgroups.
-template <bool PROT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2)))
-void gemm_pair_kernel(GemmDesc gw, GemmDesc gp, int n1) {
-  extern __shared__ __align__(16) char smem[];
-  if (int(blockIdx.x) < n1)
-    Gemm<bf16_t, float, false, false, 128, 128, PROT, 2, false>::template run<true>(
-        gw, smem, blockIdx.x, n1, 0);
-  else
-    Gemm<bf16_t, bf16_t, true, true, 128, 128, PROT, 2, PROT>::template run<true>(
-        gp, smem, int(blockIdx.x) - n1, int(gridDim.x) - n1, 1);
-}
-
-template <bool PROT>
-hipError_t pair_t(const GemmDesc& w, const GemmDesc& p, hipStream_t s) {
-  using GW = Gemm<bf16_t, float, false, false, 128, 128, PROT, 2, false>;
-  using GP = Gemm<bf16_t, bf16_t, true, true, 128, 128, PROT, 2, PROT>;
-  if (!direct_ok<bf16_t>(w, false, false) || !direct_ok<bf16_t>(p, true, true))
-    return hipErrorNotSupported;
-  if (w.nb0 * w.nb1 != 1 || p.nb0 * p.nb1 != 1 || p.splitk > 1 || w.causal != 0 ||
-      p.causal != 0)
-    return hipErrorNotSupported;
-  if (w.Br != nullptr || w.verify == 2) return hipErrorInvalidValue;  // columns only
-  // the projection's epilogue as a launch of its own would take it: the
-  // wave-local check when protected
-  if (PROT && !((p.verify <= 1 || 128 / 4 >= 32) && (p.Ac == nullptr || p.Rm <= 128)))
-    return hipErrorNotSupported;
-  const bool wcc = PROT && w.Ac != nullptr, pcc = PROT && p.Ac != nullptr;
-  const bool pcr = PROT && p.Br != nullptr;
-  const size_t lw = w.splitk > 1 ? std::max(GW::d_main_bytes(wcc, false), size_t(16 * 128 * 4))
-                                 : std::max(GW::d_main_bytes(wcc, false), GW::EPI_BYTES);
-  const size_t lp = std::max(GP::d_main_bytes(pcc, pcr), GP::EPI_BYTES);
-  const size_t lds = std::max(lw, lp);
-  const size_t lds_max =
-      std::max(std::max(GW::lds_bytes(PROT, PROT), GW::d_main_bytes(PROT, PROT)),
-               std::max(GP::lds_bytes(PROT, PROT), GP::d_main_bytes(PROT, PROT)));
-  if (lds_max > 160 * 1024) return hipErrorNotSupported;
-  const int64_t ksw = w.splitk > 1 ? w.splitk : 1;
-  const int64_t n1 = ((w.M + 127) / 128) * ((w.N + 127) / 128) * ksw;
-  const int64_t n2 = ((p.M + 127) / 128) * ((p.N + 127) / 128);
-  if (n1 == 0 || n2 == 0 || n1 % 8 != 0) return hipErrorNotSupported;  // keeps the XCD dealing
-  if (n1 + n2 > 0x7fffffff / NT) return hipErrorInvalidValue;
-  constexpr auto k = gemm_pair_kernel<PROT>;
-  hipError_t e = set_lds_limit<k>(lds_max);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k, dim3(unsigned(n1 + n2)), dim3(NT), lds, s, w, p, int(n1));
-  return hipGetLastError();
-}
-
 // The (layout, tile) pairs the attention layer launches; bf16 GEMMs with
 // fp32 output are the split-K weight gradients only.
 template <class T, class TC, bool AK, bool BKM, bool PROT>
@@ -1930,22 +1888,15 @@ hipError_t launch_splitk_reduce(const GemmDesc& g, const float* P, const float* 
   return reduce_t<bf16_t>(g, P, Pc, la, lb, stream);
 }
 
-hipError_t launch_gemm_pair(const GemmDesc& w, const GemmDesc& p, int dtype,
-                            hipStream_t stream) {
-  auto pow2 = [](int x) { return x > 0 && (x & (x - 1)) == 0; };
-  if (dtype != ABFT_BF16) return hipErrorNotSupported;
-  if (!pow2(w.Rm) || !pow2(w.Rn) || !pow2(p.Rm) || !pow2(p.Rn)) return hipErrorInvalidValue;
-  const bool pw = w.Ac != nullptr || w.Br != nullptr || w.verify != 0;
-  const bool pp = p.Ac != nullptr || p.Br != nullptr || p.verify != 0;
-  if (pw != pp) return hipErrorNotSupported;
-  return pp ? pair_t<true>(w, p, stream) : pair_t<false>(w, p, stream);
-}
-
 hipError_t launch_gemm(const GemmDesc& g, int dtype, bool c_fp32, Layout la, Layout lb,
                        Tile tile, hipStream_t stream) {
   auto pow2 = [](int x) { return x > 0 && (x & (x - 1)) == 0; };
   if (!pow2(g.Rm) || !pow2(g.Rn)) return hipErrorInvalidValue;  // the kernels shift by them
   const bool prot = g.Ac != nullptr || g.Br != nullptr || g.verify != 0;
+  if (dtype == ABFT_BF16) {
+    const hipError_t e = launch_gemm_wide(g, c_fp32, la, lb, stream);
+    if (e != hipErrorNotSupported) return e;
+  }
   if (dtype == ABFT_FP32) {
     return prot ? launch_layout<float, float, true>(g, la, lb, tile, stream)
                 : launch_layout<float, float, false>(g, la, lb, tile, stream);

@@ -1,0 +1,113 @@
+"""The layer's unbatched products on wide tiles: ragged last tiles in both
+directions, every checksum block size, whole and sliced K ranges, one launch
+and paired launches, with a fault in the last row and column of each output."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+U = 2.0 ** -8       # bf16 rounding
+EPS = 2.0 ** -24    # fp32 rounding
+
+
+def _rows(shape, op, d, H, S, B):
+    """Fault coordinates (b, h, row, col) of the last element of op's output."""
+    nh = H // d
+    if op in ("Q", "K", "V", "dCL"):
+        return (B - 1, nh - 1, S - 1, d - 1)
+    if op in ("O", "dX"):
+        return (B - 1, 0, S - 1, H - 1)
+    return (0, 0, H - 1, H - 1)
+
+
+def _close(name, got, a, b):
+    """got against the product a @ b of its stored operands: fp32 sums of K
+    terms on both sides (K eps sum|terms| each), then one rounding of got."""
+    ref, mag = a.float() @ b.float(), a.float().abs() @ b.float().abs()
+    bound = 2 * a.shape[1] * EPS * mag
+    if got.dtype == torch.bfloat16:
+        bound += U * ref.abs() * (1 + U)
+    bad = ((got.float() - ref).abs() > bound + 1e-30).sum().item()
+    assert bad == 0, f"{name}: {bad} elements outside the bound"
+
+
+# batch, seq, hidden, heads, R, fused. The first four reach 256 x 256 and 256
+# x 192 tiles (each ragged), the last two 128 x 128 with R = 32 and with K in
+# slices of uneven length.
+SHAPES = [(1, 1408, 3200, 25, 128, True), (4, 1152, 2880, 45, 128, True),
+          (4, 1088, 2816, 22, 64, False), (3, 1408, 2176, 17, 128, True),
+          (5, 640, 1088, 17, 32, True), (3, 192, 320, 5, 64, False)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B%d-S%d-H%d-%dh-R%d-f%d" % s)
+@pytest.mark.parametrize("protect", [True, False])
+def test_wide_products(shape, protect):
+    from paper_2410_11720_amd import abft
+    B, S, H, nh, R, fused = shape
+    d = H // nh
+    cfg = abft.LayerConfig(B, S, H, nh, causal=True, block_rows=R, fused=fused, protect=protect)
+    layer = abft.ProtectedAttention(cfg, capacity=256)
+    gen = torch.Generator(device="cuda").manual_seed(7)
+
+    def rand(*s, std=1.0):
+        return (torch.randn(*s, generator=gen, device="cuda") * std).bfloat16()
+    X, W, Wo, dO = rand(B, S, H), rand(H, 3 * H, std=0.02), rand(H, H, std=0.02), rand(B, S, H)
+    fwd, bwd = ("Q", "K", "V", "O"), ("dCL", "dWO", "dWQ", "dWV", "dX")
+    faults = [(op, *_rows(shape, op, d, H, S, B), float("inf")) for op in fwd + bwd] if protect else []
+    f = abft.faults_to_device(faults)
+    O = layer.forward(X, W, Wo, f)
+    dX, dW, dWo = layer.backward(dO, X, W, Wo, f)
+    torch.cuda.synchronize()
+    for rep, ops in ((layer.report, fwd), (layer.report_bwd, bwd)):
+        r = abft.read_report(rep)
+        want = [(op, *_rows(shape, op, d, H, S, B), "INF", "RECOMPUTE") for op in ops] if protect else []
+        assert sorted(r["events"]) == sorted(want)
+        assert r["n_uncorrectable"] == 0
+
+    x2, g2 = X.view(-1, H), dO.view(-1, H)
+
+    def check():
+        qkv, cl = layer.tensor("QKV").view(-1, 3 * H), layer.tensor("CL").view(-1, H)
+        dcl, dqkv = layer.tensor("dCL").view(-1, H), layer.tensor("dQKV").view(-1, 3 * H)
+        _close("QKV", qkv, x2, W)
+        _close("O", O.view(-1, H), cl, Wo)
+        _close("dCL", dcl, g2, Wo.t().contiguous())
+        _close("dWo", dWo, cl.t().contiguous(), g2)
+        _close("dWqkv", dW, x2.t().contiguous(), dqkv)
+        _close("dX", dX.view(-1, H), dqkv, W.t().contiguous())
+    check()
+    # the backward's products launched one by one
+    for t in (dX, dW, dWo):
+        t.fill_(float("nan"))
+    for stage in ("dCL", "dWo", "dWqkv", "dX"):
+        abft.attn_abft_backward_stages(cfg, dO, X, W, Wo, layer.workspace, dX, dW, dWo, None, 0,
+                                       layer.report_bwd, abft.BWD_STAGES[stage])
+        assert abft.read_report(layer.report_bwd)["n_events"] == 0
+    check()
+
+
+def test_wide_products_without_root_check():
+    """Without the root check a located element is fixed from its checksums;
+    two errors in one checksum vector are reported as uncorrectable."""
+    from paper_2410_11720_amd import abft
+    B, S, H, nh = 1, 1408, 3200, 25
+    cfg = abft.LayerConfig(B, S, H, nh, causal=True, fused=True, root_check=False)
+    layer = abft.ProtectedAttention(cfg, capacity=256)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+
+    def rand(*s, std=1.0):
+        return (torch.randn(*s, generator=gen, device="cuda") * std).bfloat16()
+    X, W, Wo, dO = rand(B, S, H), rand(H, 3 * H, std=0.02), rand(H, H, std=0.02), rand(B, S, H)
+    clean = layer.forward(X, W, Wo).clone()
+    f = abft.faults_to_device([("O", 0, 0, S - 1, 5, 3e4), ("O", 0, 0, 130, 6, float("nan")),
+                               ("O", 0, 0, 3, 7, float("inf")), ("O", 0, 0, 9, 7, float("inf"))])
+    O = layer.forward(X, W, Wo, f)
+    ev = sorted(abft.read_report(layer.report)["events"])
+    assert ev == sorted([("O", 0, 0, S - 1, 5, "NUMERIC", "DELTA"),
+                         ("O", 0, 0, 130, 6, "NAN", "RECONSTRUCT"),
+                         ("O", 0, 0, 0, 7, "-", "UNCORRECTABLE")])
+    # rebuilt from a sum of 128 rounded values: half a step of each, and the
+    # DELTA one to a step of the fault's own size (3e4 u)
+    rms = clean.float().pow(2).mean().sqrt().item()
+    assert abs(O[0, 130, 6].item() - clean[0, 130, 6].item()) <= 128 * U * 4 * rms
+    assert abs(O[0, S - 1, 5].item() - clean[0, S - 1, 5].item()) <= 3e4 * U
