@@ -7,10 +7,12 @@
 // row checksums of each Cb-column block are reduced across the lanes that
 // hold the block. The whole operand is read exactly once.
 //
-// Verifier: one workgroup per (batch, Rb-row block); one thread per vector
-// (the paper's Fig. 4 thread-per-vector mapping); a clean block costs one
-// coalesced read. Corrections use the checksums only (DELTA or
-// RECONSTRUCT), since no operands are at hand.
+// Verifier: one workgroup per (batch, Rb-row block, slab of columns). A slab
+// holds whole Cb-column blocks, so every vector of either side lies in one
+// workgroup. A clean slab costs one coalesced read, in the encoder's chunk
+// layout; a flagged one is corrected with one thread per vector (the
+// paper's Fig. 4 mapping), from the checksums only (DELTA or RECONSTRUCT),
+// since no operands are at hand.
 #include "abft_internal.hpp"
 #include "abft_device.hpp"
 
@@ -285,31 +287,114 @@ __device__ __forceinline__ void wg_sync_global() {
   __threadfence();
 }
 
-template <class T>
+// Detection over the slab of columns [c_lo, c_lo + width) of one row block,
+// each 16-byte chunk read once (thread (c, g): chunk c of rows g, g + RG, ..,
+// as in the encoder): the column sums and magnitude sums are combined over
+// the row groups in LDS, those of the Cb-column row vectors over the lanes
+// that hold them. The clean check reads the matrix and the checksums once
+// and is bound by that: 8 x 1024 x 2304 bf16 with both sides, 93 us when one
+// workgroup owned a whole row block (64 of them, two passes), VERIFY_US now.
+template <class T, int V, int CPS>
+__device__ __forceinline__ bool slab_flagged(const T* M, int64_t ld, int64_t c_lo, int width,
+                                             int64_t cols, int Rb, int Cb, const float* cc,
+                                             const float* rc, float e_rel) {
+  constexpr int RG = NT / CPS, W = CPS * V;
+  __shared__ float part[RG][W][2];
+  const int c = threadIdx.x % CPS, g = threadIdx.x / CPS;
+  const bool live = c * V < width;
+  const int64_t c0 = live ? c_lo + c * V : c_lo;  // (dead lanes read a valid chunk)
+  const int lanes = Cb / V;
+  const int64_t nrb = rc != nullptr ? cols / Cb : 0;
+  float s1[V], sa[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) s1[e] = sa[e] = 0.f;
+  bool flag = false;
+  for (int r0 = g; r0 - g < Rb; r0 += 4 * RG) {
+    // unconditional loads from clamped addresses, dropped afterwards
+    float x[4][V], c1[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int r = min(r0 + RG * u, Rb - 1);
+      load_vec<T, V>(M + r * ld + c0, x[u]);
+      c1[u] = rc != nullptr ? rc[(r * nrb + c0 / Cb) * 2] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const bool ok = live && r0 + RG * u < Rb;
+      float t1 = 0.f, ta = 0.f;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const float y = ok ? x[u][e] : 0.f;
+        s1[e] += y;
+        sa[e] += fabsf(y);
+        t1 += y;
+        ta += fabsf(y);
+      }
+      if (rc != nullptr) {
+        t1 = group_sum_n(t1, lanes);
+        ta = group_sum_n(ta, lanes);
+        flag |= ok && flagged(c1[u] - t1, ta, e_rel);
+      }
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < V; ++e) {
+    part[g][c * V + e][0] = s1[e];
+    part[g][c * V + e][1] = sa[e];
+  }
+  __syncthreads();
+  const int col = threadIdx.x;
+  if (col < width) {  // W <= NT
+    float t1 = 0.f, ta = 0.f;
+#pragma unroll
+    for (int q = 0; q < RG; ++q) {
+      t1 += part[q][col][0];
+      ta += part[q][col][1];
+    }
+    flag |= flagged(cc[c_lo + col] - t1, ta, e_rel);
+  }
+  return __syncthreads_or(flag);
+}
+
+// CPS: chunks of the fast detection (0: one thread per vector)
+template <class T, int CPS>
 __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t cols, int64_t ld,
-                                                    int64_t bstride, int Rb, int Cb,
+                                                    int64_t bstride, int Rb, int Cb, int slab,
                                                     float* col_chk, float* row_chk, float tn,
                                                     float tc, float e_rel, int op_tag,
                                                     abft_report* rep) {
   extern __shared__ __align__(16) char smem[];
-  int* rowcnt = reinterpret_cast<int*>(smem);          // [Rb][cols/Cb]
-  const int64_t b = blockIdx.y, rb = blockIdx.x;
-  const int64_t nrb = row_chk ? cols / Cb : 0;
-  int* colcnt = rowcnt + Rb * nrb;                     // [cols]
+  const int64_t nslab = (cols + slab - 1) / slab;
+  const int64_t sl = blockIdx.x % nslab, rb = blockIdx.x / nslab, b = blockIdx.y;
+  const int64_t c_lo = sl * slab, c_hi = c_lo + slab < cols ? c_lo + slab : cols;
+  const int64_t nrb = row_chk ? cols / Cb : 0;          // row blocks of a row
+  const int64_t b_lo = row_chk ? c_lo / Cb : 0;         // the slab's first
+  const int64_t nsb = row_chk ? (c_hi - c_lo) / Cb : 0; // and how many
+  int* rowcnt = reinterpret_cast<int*>(smem);           // [Rb][nsb]
+  int* colcnt = rowcnt + Rb * nsb;                      // [c_hi - c_lo]
   T* M = C + b * bstride + rb * Rb * ld;
   float* cc = col_chk + ((b * (rows / Rb) + rb) * 2) * cols;
   float* rc = row_chk ? row_chk + (b * rows + rb * Rb) * nrb * 2 : nullptr;
   const int tid = threadIdx.x;
-  for (int64_t e = tid; e < Rb * nrb + (row_chk ? cols : 0); e += NT) rowcnt[e] = 0;
+  // row vector u of the slab: row u / nsb, row block b_lo + u % nsb
+  auto rvec = [&](int64_t u) { return M + (u / nsb) * ld + (b_lo + u % nsb) * Cb; };
+  auto rchk = [&](int64_t u) { return rc + ((u / nsb) * nrb + b_lo + u % nsb) * 2; };
 
   // quick clean check: any flagged vector?
-  bool my = false;
-  for (int64_t n = tid; n < cols; n += NT)
-    my |= vec_flagged<T>(M + n, int(ld), Rb, cc[n], e_rel);
-  if (row_chk)
-    for (int64_t u = tid; u < Rb * nrb; u += NT)
-      my |= vec_flagged<T>(M + (u / nrb) * ld + (u % nrb) * Cb, 1, Cb, rc[u * 2], e_rel);
-  if (!__syncthreads_or(my)) return;
+  if constexpr (CPS > 0) {
+    if (!slab_flagged<T, 16 / sizeof(T), CPS>(M, ld, c_lo, int(c_hi - c_lo), cols, Rb, Cb, cc, rc,
+                                              e_rel))
+      return;
+  } else {
+    bool my = false;
+    for (int64_t n = c_lo + tid; n < c_hi; n += NT)
+      my |= vec_flagged<T>(M + n, int(ld), Rb, cc[n], e_rel);
+    for (int64_t u = tid; u < Rb * nsb; u += NT)
+      my |= vec_flagged<T>(rvec(u), 1, Cb, rchk(u)[0], e_rel);
+    if (!__syncthreads_or(my)) return;
+  }
+  for (int64_t e = tid; e < Rb * nsb + (row_chk ? c_hi - c_lo : 0); e += NT) rowcnt[e] = 0;
+  __syncthreads();
 
   auto fix = [&](T* vec, int stride, int n, int idx, float c1, float d1, int row, int col) {
     const float old = Storage<T>::load(vec[idx * stride]);
@@ -319,47 +404,46 @@ __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t 
     record_event(rep, op_tag, int(b), 0, row, col, classify(old, tn), action, old);
   };
   // 1. column pass
-  for (int64_t n = tid; n < cols; n += NT) {
+  for (int64_t n = c_lo + tid; n < c_hi; n += NT) {
     T* vec = M + n;
     const EecResult r = eec_locate<T>(vec, int(ld), Rb, cc[n], cc[cols + n], e_rel, tn);
     if (r.status == EEC_LOCATED) {
       fix(vec, int(ld), Rb, r.index, cc[n], r.d1, int(rb * Rb + r.index), int(n));
-      if (row_chk) atomicAdd(&rowcnt[r.index * nrb + n / Cb], 1);
+      if (row_chk) atomicAdd(&rowcnt[r.index * nsb + (n - c_lo) / Cb], 1);
     }
   }
   wg_sync_global();
   if (row_chk) {
     // 2a. refresh row checksums of 1R-corrected row vectors
-    for (int64_t u = tid; u < Rb * nrb; u += NT)
-      if (rowcnt[u] >= 2)
-        vec_checksums<T>(M + (u / nrb) * ld + (u % nrb) * Cb, 1, Cb, &rc[u * 2], &rc[u * 2 + 1]);
+    for (int64_t u = tid; u < Rb * nsb; u += NT)
+      if (rowcnt[u] >= 2) vec_checksums<T>(rvec(u), 1, Cb, rchk(u), rchk(u) + 1);
     wg_sync_global();
     // 2b. row pass
-    for (int64_t u = tid; u < Rb * nrb; u += NT) {
-      const int64_t row = u / nrb, cb = u % nrb;
-      T* vec = M + row * ld + cb * Cb;
-      const EecResult r = eec_locate<T>(vec, 1, Cb, rc[u * 2], rc[u * 2 + 1], e_rel, tn);
+    for (int64_t u = tid; u < Rb * nsb; u += NT) {
+      T* vec = rvec(u);
+      const float* k = rchk(u);
+      const EecResult r = eec_locate<T>(vec, 1, Cb, k[0], k[1], e_rel, tn);
       if (r.status == EEC_LOCATED) {
-        fix(vec, 1, Cb, r.index, rc[u * 2], r.d1, int(rb * Rb + row), int(cb * Cb + r.index));
-        atomicAdd(&colcnt[cb * Cb + r.index], 1);
+        const int64_t col = (b_lo + u % nsb) * Cb + r.index;
+        fix(vec, 1, Cb, r.index, k[0], r.d1, int(rb * Rb + u / nsb), int(col));
+        atomicAdd(&colcnt[col - c_lo], 1);
       }
     }
     wg_sync_global();
     // 2c. refresh column checksums of 1C-corrected column vectors
-    for (int64_t n = tid; n < cols; n += NT)
-      if (colcnt[n] >= 2) vec_checksums<T>(M + n, int(ld), Rb, &cc[n], &cc[cols + n]);
+    for (int64_t n = c_lo + tid; n < c_hi; n += NT)
+      if (colcnt[n - c_lo] >= 2) vec_checksums<T>(M + n, int(ld), Rb, &cc[n], &cc[cols + n]);
     wg_sync_global();
   }
   // 3. final check
-  for (int64_t n = tid; n < cols; n += NT)
+  for (int64_t n = c_lo + tid; n < c_hi; n += NT)
     if (vec_flagged<T>(M + n, int(ld), Rb, cc[n], e_rel))
       record_event(rep, op_tag, int(b), 0, int(rb * Rb), int(n), ABFT_KIND_NONE,
                    ABFT_ACT_UNCORRECTABLE, 0.f);
-  if (row_chk)
-    for (int64_t u = tid; u < Rb * nrb; u += NT)
-      if (vec_flagged<T>(M + (u / nrb) * ld + (u % nrb) * Cb, 1, Cb, rc[u * 2], e_rel))
-        record_event(rep, op_tag, int(b), 0, int(rb * Rb + u / nrb), int((u % nrb) * Cb),
-                     ABFT_KIND_NONE, ABFT_ACT_UNCORRECTABLE, 0.f);
+  for (int64_t u = tid; u < Rb * nsb; u += NT)
+    if (vec_flagged<T>(rvec(u), 1, Cb, rchk(u)[0], e_rel))
+      record_event(rep, op_tag, int(b), 0, int(rb * Rb + u / nsb), int((b_lo + u % nsb) * Cb),
+                   ABFT_KIND_NONE, ABFT_ACT_UNCORRECTABLE, 0.f);
 }
 
 __global__ void report_reset_kernel(abft_report* rep, int capacity, int set_capacity) {
@@ -506,30 +590,72 @@ hipError_t launch_encode_jobs(const EncodeJob* jobs, int n, int dtype, abft_repo
   return encode_jobs_t<bf16_t>(live, m, reset, s);
 }
 
+namespace {
+template <class T, int CPS>
+hipError_t verify_t(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t bs,
+                    int Rb, int Cb, int64_t slab, float* col_chk, float* row_chk, float tn,
+                    float tc, float e_rel, int op_tag, abft_report* report, hipStream_t s) {
+  const size_t lds = row_chk ? size_t(Rb * (slab / Cb) + slab) * sizeof(int) : 0;
+  auto k = verify_kernel<T, CPS>;
+  if (lds > 32 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid(unsigned((cols + slab - 1) / slab * (rows / Rb)), unsigned(batch));
+  hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, C, rows, cols, ld, bs, Rb, Cb, int(slab), col_chk,
+                     row_chk, tn, tc, e_rel, op_tag, report);
+  return hipGetLastError();
+}
+
+// The chunked detection takes what the encoder's vector path takes (aligned
+// rows, row blocks of a power of two of at most 16 chunks); slabs of 8
+// chunks, 16 where a row block needs them. Any other shape: one thread per
+// vector over slabs of about 256 columns. Where the correction's counters
+// would not fit beside the detection's LDS, or the slabs of a launch not its
+// grid, a workgroup takes whole rows.
+template <class T>
+hipError_t verify_d(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t bs, int Rb,
+                    int Cb, float* col_chk, float* row_chk, float tn, float tc, float e_rel,
+                    int op_tag, abft_report* report, hipStream_t s) {
+  constexpr int V = 16 / sizeof(T);
+  bool fast = reinterpret_cast<uintptr_t>(C) % 16 == 0 && ld % V == 0 && cols % V == 0 && bs % V == 0;
+  int cps = 8;
+  if (row_chk != nullptr) {
+    const int l = Cb / V;
+    fast = fast && Cb % V == 0 && l >= 1 && (l & (l - 1)) == 0 && l <= 16;
+    cps = l > 8 ? 16 : 8;
+  }
+  int64_t slab = fast ? cps * V : (row_chk != nullptr ? (255 / Cb + 1) * int64_t(Cb) : 256);
+  slab = slab < cols ? slab : cols;
+  const int64_t counters = row_chk != nullptr ? Rb * (slab / Cb) + slab : 0;
+  fast = fast && counters <= 128 * 1024 / 4;
+  if (!fast && counters > 150 * 1024 / 4) slab = cols;
+  if ((cols + slab - 1) / slab * (rows / Rb) > (int64_t(1) << 24) - 1) {
+    fast = false;
+    slab = cols;
+  }
+  if (fast && cps == 8)
+    return verify_t<T, 8>(C, batch, rows, cols, ld, bs, Rb, Cb, slab, col_chk, row_chk, tn, tc,
+                          e_rel, op_tag, report, s);
+  if (fast)
+    return verify_t<T, 16>(C, batch, rows, cols, ld, bs, Rb, Cb, slab, col_chk, row_chk, tn, tc,
+                           e_rel, op_tag, report, s);
+  return verify_t<T, 0>(C, batch, rows, cols, ld, bs, Rb, Cb, slab, col_chk, row_chk, tn, tc, e_rel,
+                        op_tag, report, s);
+}
+}  // namespace
+
 hipError_t launch_verify(void* C, int dtype, int64_t batch, int64_t rows, int64_t cols,
                          int64_t ld, int64_t batch_stride, int Rb, int Cb, float* col_chk,
                          float* row_chk, float tn, float tc, float e_rel, int op_tag,
                          abft_report* report, hipStream_t s) {
   if (batch == 0 || rows == 0 || cols == 0) return hipSuccess;
-  const int64_t nrb = row_chk ? cols / Cb : 0;
-  const size_t lds = size_t(Rb * nrb + (row_chk ? cols : 0)) * sizeof(int);
-  dim3 grid(rows / Rb, batch);
-  if (dtype == ABFT_FP32) {
-    auto k = verify_kernel<float>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, static_cast<float*>(C), rows, cols, ld,
-                       batch_stride, Rb, Cb, col_chk, row_chk, tn, tc, e_rel, op_tag, report);
-  } else {
-    auto k = verify_kernel<bf16_t>;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, static_cast<bf16_t*>(C), rows, cols, ld,
-                       batch_stride, Rb, Cb, col_chk, row_chk, tn, tc, e_rel, op_tag, report);
-  }
-  return hipGetLastError();
+  if (dtype == ABFT_FP32)
+    return verify_d<float>(static_cast<float*>(C), batch, rows, cols, ld, batch_stride, Rb, Cb,
+                           col_chk, row_chk, tn, tc, e_rel, op_tag, report, s);
+  return verify_d<bf16_t>(static_cast<bf16_t*>(C), batch, rows, cols, ld, batch_stride, Rb, Cb,
+                          col_chk, row_chk, tn, tc, e_rel, op_tag, report, s);
 }
 
 hipError_t launch_report_reset(abft_report* report, int capacity, bool set_capacity,
