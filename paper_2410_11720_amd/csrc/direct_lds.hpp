@@ -100,6 +100,30 @@ struct Direct {
     }
   }
 
+  // the last stage of a K range that ends at kend < k0 + 64: k past it reads
+  // the range's last chunk or row (the caller does not multiply it)
+  __device__ static __forceinline__ void issue_tail(const bf16_t* base, int64_t ld, int row0,
+                                                    int nrows, int k0, int kend, char* st, int wave,
+                                                    int lane) {
+#pragma unroll
+    for (int j = 0; j < PER_WAVE; ++j) {
+      const int i = wave * PER_WAVE + j;
+      const bf16_t* src;
+      if constexpr (KMAJ) {
+        const int row = i * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ (row & 7);
+        src = base + int64_t(min(row0 + row, nrows - 1)) * ld + min(k0 + c * 8, kend - 8);
+      } else {
+        constexpr int CPR = ROWS / 8;
+        constexpr int KR = 64 / CPR;
+        const int kr = i * KR + lane / CPR;
+        const int c = (lane % CPR) ^ (2 * (kr & 3));
+        src = base + int64_t(min(k0 + kr, kend - 1)) * ld + min(row0 + c * 8, nrows - 8);
+      }
+      __builtin_amdgcn_global_load_lds(src, (lds_void*)(st + i * 1024), 16, 0, 0);
+    }
+  }
+
   // MFMA 16x16x32 operand fragment: rows rb + (lane & 15), k = kk + 8 (lane >> 4) + 0..7
   // (K-major image: a plain LDS read)
   __device__ static __forceinline__ bf16x8 frag(const char* st, int rb, int kk, int lane) {

@@ -88,28 +88,19 @@ struct TileLoader {
   static constexpr int PER = KMAJ ? (CHUNKS + NT - 1) / NT : ((NBLK + NT - 1) / NT) * VEC;
   uint4 reg[PER];
 
+  // Every load is unconditional, from a clamped (valid) address: a load under
+  // a divergent branch is waited for at the join, one at a time. Rows past
+  // nrows repeat the last ones (their results are never stored); k past kend
+  // is zeroed by store().
   __device__ void load(const T* base, int64_t ld, int row0, int nrows, int k0, int kend,
                        int tid) {
-    // interior tiles (the common case) skip the per-chunk bounds tests
-    const bool full = row0 + ROWS <= nrows && k0 + BK <= kend;
     if constexpr (KMAJ) {
-      if (full && CHUNKS % NT == 0) {
-#pragma unroll
-        for (int p = 0; p < PER; ++p) {
-          const int c = tid + p * NT;
-          const int r = c / (BK / VEC), kc = (c % (BK / VEC)) * VEC;
-          reg[p] = *reinterpret_cast<const uint4*>(base + op_off<true>(row0 + r, k0 + kc, ld));
-        }
-        return;
-      }
 #pragma unroll
       for (int p = 0; p < PER; ++p) {
         const int c = tid + p * NT;
         const int r = c / (BK / VEC), kc = (c % (BK / VEC)) * VEC;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (c < CHUNKS && row0 + r < nrows && k0 + kc < kend)
-          v = *reinterpret_cast<const uint4*>(base + op_off<true>(row0 + r, k0 + kc, ld));
-        reg[p] = v;
+        reg[p] = *reinterpret_cast<const uint4*>(
+            base + op_off<true>(min(row0 + r, nrows - 1), min(k0 + kc, kend - VEC), ld));
       }
     } else {
 #pragma unroll
@@ -117,40 +108,39 @@ struct TileLoader {
         const int blk = tid + p * NT;
         const int rb = blk % NRB, kb = blk / NRB;
 #pragma unroll
-        for (int s = 0; s < VEC; ++s) {
-          uint4 v = make_uint4(0, 0, 0, 0);
-          if (blk < NBLK && row0 + rb * VEC < nrows && k0 + kb * VEC + s < kend)
-            v = *reinterpret_cast<const uint4*>(
-                base + op_off<false>(row0 + rb * VEC, k0 + kb * VEC + s, ld));
-          reg[p * VEC + s] = v;
-        }
+        for (int s = 0; s < VEC; ++s)
+          reg[p * VEC + s] = *reinterpret_cast<const uint4*>(
+              base + op_off<false>(min(row0 + rb * VEC, nrows - VEC), min(k0 + kb * VEC + s, kend - 1), ld));
       }
     }
   }
 
-  __device__ void store(T* lds, int tid) {
+  // writes the stage loaded for k0
+  __device__ void store(T* lds, int k0, int kend, int tid) {
     if constexpr (KMAJ) {
 #pragma unroll
       for (int p = 0; p < PER; ++p) {
         const int c = tid + p * NT;
-        if (c < CHUNKS) {
+        if (CHUNKS % NT == 0 || c < CHUNKS) {
           const int r = c / (BK / VEC), kc = (c % (BK / VEC)) * VEC;
-          *reinterpret_cast<uint4*>(lds + r * LDK + kc) = reg[p];
+          *reinterpret_cast<uint4*>(lds + r * LDK + kc) =
+              k0 + kc < kend ? reg[p] : make_uint4(0, 0, 0, 0);
         }
       }
     } else {
 #pragma unroll
       for (int p = 0; p < PER / VEC; ++p) {
         const int blk = tid + p * NT;
-        if (blk >= NBLK) continue;
+        if (NBLK % NT != 0 && blk >= NBLK) continue;
         const int rb = blk % NRB, kb = blk / NRB;
         uint32_t in[VEC][4];
 #pragma unroll
         for (int s = 0; s < VEC; ++s) {
-          in[s][0] = reg[p * VEC + s].x;
-          in[s][1] = reg[p * VEC + s].y;
-          in[s][2] = reg[p * VEC + s].z;
-          in[s][3] = reg[p * VEC + s].w;
+          const bool in_k = k0 + kb * VEC + s < kend;
+          in[s][0] = in_k ? reg[p * VEC + s].x : 0u;
+          in[s][1] = in_k ? reg[p * VEC + s].y : 0u;
+          in[s][2] = in_k ? reg[p * VEC + s].z : 0u;
+          in[s][3] = in_k ? reg[p * VEC + s].w : 0u;
         }
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {  // output row rb*VEC + e, k = kb*VEC + [0, VEC)
@@ -196,7 +186,8 @@ struct StripLoader {
     if (KMAJ) { r = e / BK; k = e % BK; }
     else { r = e % NR; k = e / NR; }
   }
-  // rows r0 + r exist only for r < nvalid (the last tile may be ragged)
+  // rows r0 + r exist only for r < nvalid >= 1 (the last tile may be ragged:
+  // rows past it repeat the last one); unconditional loads, as the tiles'
   __device__ void load(const float* base, int64_t ld, int r0, int nvalid, int k0, int kend,
                        int tid) {
 #pragma unroll
@@ -204,25 +195,24 @@ struct StripLoader {
       const int e = tid + p * NT;
       int r, k;
       rk(e, r, k);
-      float v = 0.f;
-      if (r < nvalid && k0 + k < kend) v = base[op_off<KMAJ>(r0 + r, k0 + k, ld)];
-      reg[p] = v;
+      reg[p] = base[op_off<KMAJ>(r0 + max(min(r, nvalid - 1), 0), min(k0 + k, kend - 1), ld)];
     }
   }
-  __device__ void store(T* lds, int nc, int tid) {
+  __device__ void store(T* lds, int nc, int nvalid, int k0, int kend, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
       const int e = tid + p * NT;
       int r, k;
       rk(e, r, k);
       if (r < nc) {
+        const float v = r < nvalid && k0 + k < kend ? reg[p] : 0.f;
         if constexpr (sizeof(T) == 2) {
-          const bf16_t hi = f2bf(reg[p]);
-          const bf16_t lo = f2bf(reg[p] - bf2f(hi));
+          const bf16_t hi = f2bf(v);
+          const bf16_t lo = f2bf(v - bf2f(hi));
           lds[(2 * r) * LDK + k] = hi;
           lds[(2 * r + 1) * LDK + k] = lo;
         } else {
-          lds[r * LDK + k] = reg[p];
+          lds[r * LDK + k] = v;
         }
       }
     }
@@ -620,8 +610,14 @@ struct Gemm {
         auto slot = [&](int kt) { return smem + (kt % NSTAGE) * DST; };
         auto issue_dir = [&](int kt) {
           char* st = slot(kt);
-          DA::issue(Ab, g.lda, m0, g.M, k_lo + kt * BK, st, wave, lane);
-          DB::issue(Bb, g.ldb, n0, g.N, k_lo + kt * BK, st + DA_BYTES, wave, lane);
+          const int kn = k_lo + kt * BK;
+          if (kn + BK <= k_hi) {
+            DA::issue(Ab, g.lda, m0, g.M, kn, st, wave, lane);
+            DB::issue(Bb, g.ldb, n0, g.N, kn, st + DA_BYTES, wave, lane);
+          } else {  // the half stage at the end of a K range (K % 64 == 32)
+            DA::issue_tail(Ab, g.lda, m0, g.M, kn, k_hi, st, wave, lane);
+            DB::issue_tail(Bb, g.ldb, n0, g.N, kn, k_hi, st + DA_BYTES, wave, lane);
+          }
         };
         auto issue_strip = [&](int kt) {
           const int kn = k_lo + kt * BK;
@@ -630,8 +626,9 @@ struct Gemm {
         };
         auto commit_strip = [&](int kt) {
           T* st = reinterpret_cast<T*>(slot(kt) + DA_BYTES + DB_BYTES);
-          if (cc && !img) ls.store(st, nc, tid);
-          if (cr && !imgr) lr.store(st + r_off, nq, tid);
+          const int kn = k_lo + kt * BK;
+          if (cc && !img) ls.store(st, nc, nc_valid, kn, k_hi, tid);
+          if (cr && !imgr) lr.store(st + r_off, nq, nq_valid, kn, k_hi, tid);
         };
         // the strips from their images: the column strip's rows go to
         // waves 0.., the row strip's to the waves after them; a wave copies
@@ -642,7 +639,7 @@ struct Gemm {
           if (img && wave < wc) {
             const int r = min(wave * 8 + (lane >> 3), 2 * nc_valid - 1);
             const uint16_t* src =
-                g.Aci + int64_t(2 * rc0 + r) * g.ldaci + k_lo + kt * BK + (lane & 7) * 8;
+                g.Aci + int64_t(2 * rc0 + r) * g.ldaci + min(k_lo + kt * BK + (lane & 7) * 8, g.K - 8);
             __builtin_amdgcn_global_load_lds(
                 src, (lds_void*)(slot(kt) + DA_BYTES + DB_BYTES + wave * 1024), 16, 0, 0);
           }
@@ -650,18 +647,19 @@ struct Gemm {
             const int w = wave - wc;
             const int r = min(w * 8 + (lane >> 3), 2 * nq_valid - 1);
             const uint16_t* src =
-                g.Bri + int64_t(2 * qc0 + r) * g.ldbri + k_lo + kt * BK + (lane & 7) * 8;
+                g.Bri + int64_t(2 * qc0 + r) * g.ldbri + min(k_lo + kt * BK + (lane & 7) * 8, g.K - 8);
             __builtin_amdgcn_global_load_lds(
                 src,
                 (lds_void*)(slot(kt) + DA_BYTES + DB_BYTES + r_off * int(sizeof(T)) + w * 1024),
                 16, 0, 0);
           }
         };
-        auto compute_d = [&](const char* st) {
+        auto compute_d = [&](const char* st, int kleft) {
           const T* sS = reinterpret_cast<const T*>(st + DA_BYTES + DB_BYTES);
           const T* sR = sS + r_off;
 #pragma unroll
           for (int kk = 0; kk < BK; kk += KI) {
+            if (kk >= kleft) break;  // (half stage: its second half is not there)
             typename Mfma<T>::frag af[IM], bfr[JN];
             // MN-major images are read with transposing reads that are
             // waited for together
@@ -702,7 +700,7 @@ struct Gemm {
             wait_vmcnt<0>();
             if (PROT) commit_strip(kt);
             __syncthreads();
-            compute_d(slot(kt));
+            compute_d(slot(kt), k_hi - k_lo - kt * BK);
             __syncthreads();
           }
         } else {
@@ -725,7 +723,7 @@ struct Gemm {
               issue_dir(kt + NSTAGE - 1);
               if (PROT) issue_img(kt + NSTAGE - 1);
             }
-            compute_d(slot(kt));
+            compute_d(slot(kt), k_hi - k_lo - kt * BK);
           }
           __syncthreads();  // the epilogue reuses the stages
         }
@@ -736,10 +734,10 @@ struct Gemm {
       lb.load(B, g.ldb, n0, g.N, k_lo, k_hi, tid);
       if (cc) ls.load(Ac, g.ldac, rc0, nc_valid, k_lo, k_hi, tid);
       if (cr) lr.load(Br, g.ldbr, qc0, nq_valid, k_lo, k_hi, tid);
-      la.store(lds, tid);
-      lb.store(lds + A_ELEMS, tid);
-      if (cc) ls.store(lds + A_ELEMS + B_ELEMS, nc, tid);
-      if (cr) lr.store(lds + A_ELEMS + B_ELEMS + r_off, nq, tid);
+      la.store(lds, k_lo, k_hi, tid);
+      lb.store(lds + A_ELEMS, k_lo, k_hi, tid);
+      if (cc) ls.store(lds + A_ELEMS + B_ELEMS, nc, nc_valid, k_lo, k_hi, tid);
+      if (cr) lr.store(lds + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, k_lo, k_hi, tid);
       __syncthreads();
     }
 
@@ -773,10 +771,11 @@ struct Gemm {
       if (more) {
         if (NSTAGE == 1) __syncthreads();  // every wave is done reading the one stage
         T* nA = lds + (NSTAGE >= 2 ? (cur ^ 1) : 0) * STAGE;
-        la.store(nA, tid);
-        lb.store(nA + A_ELEMS, tid);
-        if (cc) ls.store(nA + A_ELEMS + B_ELEMS, nc, tid);
-        if (cr) lr.store(nA + A_ELEMS + B_ELEMS + r_off, nq, tid);
+        const int kn = k_lo + (kt + 1) * BK;
+        la.store(nA, kn, k_hi, tid);
+        lb.store(nA + A_ELEMS, kn, k_hi, tid);
+        if (cc) ls.store(nA + A_ELEMS + B_ELEMS, nc, nc_valid, kn, k_hi, tid);
+        if (cr) lr.store(nA + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, kn, k_hi, tid);
       }
       __syncthreads();
     }
@@ -1537,13 +1536,13 @@ void gemm_kernel(GemmDesc g) {
                                                                       gridDim.x, 0);
 }
 
-// The direct-to-LDS path needs bf16 operands, K ranges of whole 64-wide
-// stages (K a multiple of 64; causal K ranges and split-K slices then are
-// too), 16-byte aligned operand rows, and whole 8-element chunks along the
+// The direct-to-LDS path needs bf16 operands, K ranges of whole 32-wide
+// half stages (K a multiple of 32; causal K ranges and split-K slices then
+// are too), 16-byte aligned operand rows, and whole 8-element chunks along the
 // M or N extent of an MN-major operand.
 template <class T>
 bool direct_ok(const GemmDesc& g, bool ak, bool bk) {
-  if (sizeof(T) != 2 || g.K % 64 != 0) return false;
+  if (sizeof(T) != 2 || g.K % 32 != 0) return false;
   auto al = [](const void* p, int64_t ld, int64_t s0, int64_t s1) {
     return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
   };
