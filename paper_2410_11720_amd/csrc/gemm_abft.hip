@@ -26,7 +26,16 @@ namespace abft {
 
 namespace {
 
-constexpr int NT = 256;  // threads per workgroup: 4 waves as 2 (M) x 2 (N)
+// Threads per workgroup: four waves, eight for fp32 operands. An fp32 MFMA
+// takes 32 cycles for 2048 flop, so LDS and L2 keep up with small tiles, but a
+// protected 128 x 128 fp32 tile fills more than half the LDS: with four waves
+// that was one per SIMD, each waiting out its own LDS latency and barriers
+// (T 4096 H 2048 fp32 QKV 1535 -> 1250 us; unprotected, where two workgroups
+// of four waves fit, the same within 3%).
+template <class T>
+constexpr int threads_of() {
+  return sizeof(T) == 4 ? 512 : 256;
+}
 
 // The kernel's descriptor (argument `slot` of the kernel: the descriptors
 // are its first arguments), reached through an opaque copy of the
@@ -56,14 +65,19 @@ template <> struct Mfma<bf16_t> {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
 };
+// A step of 16 k in four 16x16x4 MFMAs: a lane holds four consecutive k (one
+// 16-byte LDS read), MFMA e takes element e of every lane, i.e. k = 4 g + e of
+// the lane groups g (the same order in both operands).
 template <> struct Mfma<float> {
   static constexpr int BK = 32;
-  static constexpr int KI = 4;
+  static constexpr int KI = 16;
   static constexpr int PAD = 4;
-  typedef float frag;
-  __device__ static frag load(const float* p) { return *p; }
-  __device__ static floatx4 mma(frag a, frag b, floatx4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  typedef floatx4 frag;
+  __device__ static frag load(const float* p) { return *reinterpret_cast<const frag*>(p); }
+  __device__ static floatx4 mma(const frag& a, const frag& b, floatx4 c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+    return c;
   }
 };
 
@@ -78,7 +92,7 @@ __device__ __forceinline__ int64_t op_off(int64_t row, int64_t k, int64_t ld) {
 // layout. A K-major source is copied in 16-byte chunks; an MN-major source
 // is read as VEC x VEC blocks (VEC rows of k, VEC consecutive rows each),
 // one block per thread, and transposed in registers.
-template <class T, bool KMAJ, int ROWS>
+template <class T, bool KMAJ, int ROWS, int NT>
 struct TileLoader {
   static constexpr int BK = Mfma<T>::BK;
   static constexpr int LDK = BK + Mfma<T>::PAD;
@@ -169,7 +183,7 @@ struct TileLoader {
 // lo row each, interleaved (row 2r hi, 2r + 1 lo): the strip rows of
 // checksum block b are 4b (hi c1), 4b + 1 (lo c1), 4b + 2 (hi c2), 4b + 3
 // (lo c2).
-template <class T, bool KMAJ>
+template <class T, bool KMAJ, int NT>
 struct StripLoader {
   static constexpr int BK = Mfma<T>::BK;
   static constexpr int LDK = BK + Mfma<T>::PAD;
@@ -367,17 +381,18 @@ __device__ __forceinline__ TileIdx tile_of(const GemmDesc& g, int lin, int total
 template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE,
           bool WLC = false>
 struct Gemm {
+  static constexpr int NT = threads_of<T>();
   static constexpr int BK = Mfma<T>::BK;
   static constexpr int KI = Mfma<T>::KI;
   static constexpr int LDK = BK + Mfma<T>::PAD;
-  static constexpr int WGN = WLC ? 4 : 2, WGM = 4 / WGN;  // wave grid
+  static constexpr int WGN = WLC ? 4 : 2, WGM = NT / 64 / WGN;  // wave grid
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int IM = WM / 16, JN = WN / 16;
   // strip blocks per wave: column strips of the wave's own columns (WLC)
-  // or split between the two waves sharing them; row strips split between
+  // or split between the waves sharing them; row strips split between
   // the waves sharing the rows
-  static constexpr int JS = WLC ? JN : JN / 2, IS = IM / WGN;
-  static_assert(WLC ? (IM >= 4 && JN >= 1) : (IM >= 2 && JN >= 2), "tile too small");
+  static constexpr int JS = (JN + WGM - 1) / WGM, IS = (IM + WGN - 1) / WGN;
+  static_assert(WLC ? (IM >= 4 && JN >= 1) : (IM >= 2 && JN >= 1), "tile too small");
   static constexpr int FRAG = KI / 4;  // operand elements per lane
   // bf16 operands and bf16 output: detection sums on the matrix cores
   static constexpr bool MSUM = PROT && sizeof(T) == 2 && sizeof(TC) == 2;
@@ -497,10 +512,10 @@ struct Gemm {
     const bool g_cc = PROT && g.Ac != nullptr, g_cr = PROT && g.Br != nullptr;
     const int STAGE = stage_elems(g_cc, g_cr);
     const int r_off = g_cc ? S_ELEMS : 0;
-    TileLoader<T, AK, BM> la;
-    TileLoader<T, BKM, BN> lb;
-    StripLoader<T, AK> ls;
-    StripLoader<T, BKM> lr;
+    TileLoader<T, AK, BM, NT> la;
+    TileLoader<T, BKM, BN, NT> lb;
+    StripLoader<T, AK, NT> ls;
+    StripLoader<T, BKM, NT> lr;
 
     floatx4 acc[IM][JN];
 #pragma unroll
@@ -535,17 +550,17 @@ struct Gemm {
     }
     const int soff = img ? (fr & (2 * nc - 1)) * BK + fk : fr * LDK + fk;
     const int roff = imgr ? (fr & (2 * nq - 1)) * BK + fk : fr * LDK + fk;
+    // the waves' positions in the wave grid as scalars: the strip blocks a
+    // wave multiplies are chosen by uniform branches, so every fragment
+    // index stays a compile-time constant (a runtime index would send the
+    // arrays to scratch) and no per-lane selects are spent on them
+    const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
     auto strip_frags = [&](const T* st0, const T* sS, const T* sR, int kk, Frag& sf, Frag& rf) {
       if (PROT && EARLY) {
         sf = Mfma<T>::load((cc ? sS + soff : st0 + fr * LDK + fk) + kk);
         if (cr) rf = Mfma<T>::load(sR + roff + kk);
       }
     };
-    // the waves' positions in the wave grid as scalars: the strip blocks a
-    // wave multiplies are chosen by uniform branches, so every fragment
-    // index stays a compile-time constant (a runtime index would send the
-    // arrays to scratch) and no per-lane selects are spent on them
-    const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
     // the MFMAs of one KI-wide k step: the tile, then the checksum strips
     auto mma_kk = [&](const Frag (&af)[IM], const Frag (&bfr)[JN], const Frag& sf,
                       const Frag& rf, const T* sS, const T* sR, int kk) {
@@ -558,7 +573,9 @@ struct Gemm {
           const auto sfl = Mfma<T>::load(sS + fr * LDK + kk + fk);
 #pragma unroll
           for (int j = 0; j < JS; ++j) {
-            const auto bsel = (WLC || wm == 0) ? bfr[j] : bfr[WLC ? j : JS + j];
+            auto bsel = bfr[j];
+#pragma unroll
+            for (int w = 1; w < WGM; ++w) bsel = wm == w ? bfr[min(w * JS + j, JN - 1)] : bsel;
             accs[j] = Mfma<T>::mma(sfl, bsel, accs[j]);
           }
         }
@@ -568,27 +585,28 @@ struct Gemm {
           for (int i = 0; i < IS; ++i) {
             auto asel = af[i];
 #pragma unroll
-            for (int w = 1; w < WGN; ++w) asel = wn == w ? af[IS * w + i] : asel;
+            for (int w = 1; w < WGN; ++w) asel = wn == w ? af[min(IS * w + i, IM - 1)] : asel;
             accr[i] = Mfma<T>::mma(rfl, asel, accr[i]);
           }
         }
       }
       if (PROT && EARLY) {
         if (cc) {
-          if (WLC || wmu == 0) {
 #pragma unroll
-            for (int j = 0; j < JS; ++j) accs[j] = Mfma<T>::mma(sf, bfr[j], accs[j]);
-          } else {
+          for (int w = 0; w < WGM; ++w)
+            if (wmu == w) {
 #pragma unroll
-            for (int j = 0; j < JS; ++j) accs[j] = Mfma<T>::mma(sf, bfr[WLC ? j : JS + j], accs[j]);
-          }
+              for (int j = 0; j < JS; ++j)
+                if (w * JS + j < JN) accs[j] = Mfma<T>::mma(sf, bfr[w * JS + j], accs[j]);
+            }
         }
         if (cr) {
 #pragma unroll
           for (int w = 0; w < WGN; ++w)
             if (wnu == w) {
 #pragma unroll
-              for (int i = 0; i < IS; ++i) accr[i] = Mfma<T>::mma(rf, af[IS * w + i], accr[i]);
+              for (int i = 0; i < IS; ++i)
+                if (IS * w + i < IM) accr[i] = Mfma<T>::mma(rf, af[IS * w + i], accr[i]);
             }
         }
       }
@@ -804,7 +822,8 @@ struct Gemm {
         for (int j = 0; j < JS; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r)
-            CsL[((lane >> 4) * 4 + r) * BN + wn * WN + (wm * JS + j) * 16 + fr] = accs[j][r];
+            if (wm * JS + j < JN)
+              CsL[((lane >> 4) * 4 + r) * BN + wn * WN + (wm * JS + j) * 16 + fr] = accs[j][r];
         __syncthreads();
         float* Cc = g.Cc + b0 * g.sCc0 + b1 * g.sCc1 + int64_t(kslice) * g.sCck;
         const int ncb = BM >> __builtin_ctz(g.Rm);
@@ -862,16 +881,16 @@ struct Gemm {
       for (int j = 0; j < JS; ++j)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          CsL[((lane >> 4) * 4 + r) * BN + wn * WN + (wm * JS + j) * 16 + fr] =
-              accs[j][r];
+          if (wm * JS + j < JN)
+            CsL[((lane >> 4) * 4 + r) * BN + wn * WN + (wm * JS + j) * 16 + fr] = accs[j][r];
     }
     if (PROT && cr && !WLC) {
 #pragma unroll
       for (int i = 0; i < IS; ++i)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-          RsL[(wm * WM + (wn * IS + i) * 16 + fr) * 16 + (lane >> 4) * 4 + r] =
-              accr[i][r];
+          if (wn * IS + i < IM)
+            RsL[(wm * WM + (wn * IS + i) * 16 + fr) * 16 + (lane >> 4) * 4 + r] = accr[i][r];
     }
     // injected faults (test-only): written into the rounded tile before any
     // verification
@@ -1522,14 +1541,17 @@ struct Gemm {
 // three (at most 168 registers) to hide its loads behind the other
 // workgroups' work: unprotected, or protected with the wave-local check on
 // the direct path (a few spills, far cheaper than the lost workgroup).
-template <class T, int BM, int BN, bool PROT, int NSTAGE, bool WLC>
+// fp32 tiles of 128 x 64 or less, and the weight gradients (whose K slices
+// need the operand stages only): two workgroups of eight waves.
+template <class T, bool WGRAD, int BM, int BN, bool PROT, int NSTAGE, bool WLC>
 constexpr int gemm_waves_per_eu() {
+  if (sizeof(T) == 4) return BN <= 64 || WGRAD ? 4 : 2;
   return BM * BN > 128 * 128 ? 1 : (sizeof(T) == 2 && NSTAGE == 1 && (!PROT || WLC) ? 3 : 2);
 }
 
 template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, bool DIR,
           bool WLC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, BM, BN, PROT, NSTAGE, WLC && DIR>())))
+__global__ __launch_bounds__(threads_of<T>()) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && DIR>())))
 void gemm_kernel(GemmDesc g) {
   extern __shared__ __align__(16) char smem[];
   Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, WLC>::template run<DIR>(g, smem, blockIdx.x,
@@ -1623,9 +1645,26 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   if (nb > 1 && ks > 1) return hipErrorInvalidValue;  // split-K is for unbatched GEMMs
   if (ks > 1 && sizeof(TC) != 4) return hipErrorInvalidValue;  // fp32 partial slices
   const int64_t total = tiles * nb * ks;
-  if (total > 0x7fffffff / NT) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3(unsigned(total)), dim3(NT), lds, s, g);
+  if (total > 0x7fffffff / G::NT) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3(unsigned(total)), dim3(G::NT), lds, s, g);
   return hipGetLastError();
+}
+
+// Columns of an fp32 tile (128 rows): the width at which the CUs' rounds of
+// tiles cost least, a narrower tile paying for reading A more often. A row
+// checksum block lies in one tile.
+int f32_columns(const GemmDesc& g, int most) {
+  int best = most;
+  double t = -1;
+  for (int bn = most; bn >= 32; bn /= 2) {
+    if (g.verify == 2 && g.Rn > bn) break;
+    if (g.Br != nullptr && (g.Rn > bn || g.cr_n_begin % bn != 0)) break;
+    const int64_t tiles = int64_t((g.M + 127) / 128) * ((g.N + bn - 1) / bn) * g.nb0 * g.nb1 *
+                          (g.splitk > 1 ? g.splitk : 1);
+    const double c = double((tiles + 255) / 256) * bn * (bn == 128 ? 1.0 : bn == 64 ? 1.1 : 1.25);
+    if (t < 0 || c < t) { t = c; best = bn; }
+  }
+  return best;
 }
 
 // The (layout, tile) pairs the attention layer launches; bf16 GEMMs with
@@ -1638,13 +1677,20 @@ hipError_t launch_tile(const GemmDesc& g, Tile tile, hipStream_t s) {
       if (tile == Tile::T128x128) return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
     return hipErrorInvalidValue;
   } else {
-    if (tile == Tile::T128x128) return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
-    if constexpr (AK && BKM) {
+    if constexpr (AK && BKM)
       if (tile == Tile::T128x128S1) return launch_t<T, TC, AK, BKM, 128, 128, PROT, 1>(g, s);
+    if constexpr (sizeof(T) == 4) {
+      switch (f32_columns(g, tile == Tile::T128x64 ? 64 : 128)) {
+        case 32: return launch_t<T, TC, AK, BKM, 128, 32, PROT>(g, s);
+        case 64: return launch_t<T, TC, AK, BKM, 128, 64, PROT>(g, s);
+      }
+      return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
     } else {
-      if (tile == Tile::T128x64) return launch_t<T, TC, AK, BKM, 128, 64, PROT>(g, s);
+      if (tile == Tile::T128x128) return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
+      if constexpr (!AK || !BKM)
+        if (tile == Tile::T128x64) return launch_t<T, TC, AK, BKM, 128, 64, PROT>(g, s);
+      return hipErrorInvalidValue;
     }
-    return hipErrorInvalidValue;
   }
 }
 

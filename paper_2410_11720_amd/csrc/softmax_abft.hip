@@ -22,8 +22,6 @@
 namespace abft {
 namespace {
 
-constexpr int NT = 256;
-
 template <class T> struct Vec;
 template <> struct Vec<bf16_t> {
   static constexpr int N = 8;
@@ -107,12 +105,14 @@ __device__ __forceinline__ void round_chunk(float (&x)[4], uint4& bits) {
 
 // CH: 16-byte chunks per lane per row (S <= 64 * CH * VEC); RPI rows per
 // iteration per wave; PF: prefetch the next iteration's rows; CHK: encode
-// the checksums (some of col_chk, row_chk given).
-template <class T, int CH, bool BWD, int RPI, bool PF, bool CHK>
-__global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
+// the checksums (some of col_chk, row_chk given); NW: waves per workgroup
+// (see launch_sm).
+template <class T, int CH, bool BWD, int RPI, bool PF, bool CHK, int NW>
+__global__ __launch_bounds__(64 * NW) void softmax_kernel(SoftmaxDesc d) {
+  constexpr int NT = 64 * NW;
   constexpr int V = Vec<T>::N;
   extern __shared__ __align__(16) char smem[];
-  float* colacc = reinterpret_cast<float*>(smem);  // [8][S]
+  float* colacc = reinterpret_cast<float*>(smem);  // [2 NW][S]
 
   // the wave index is uniform over the wave: row indices and row
   // addresses stay in scalar registers
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
     for (int e = 0; e < V; ++e) c1[t][e] = c2[t][e] = 0.f;
 
   const float l2e = 1.4426950408889634f;
-  // Rows of this wave: rl = wave + 4 * (it * RPI + u), u < RPI. With PF the
+  // Rows of this wave: rl = wave + NW * (it * RPI + u), u < RPI. With PF the
   // loads of iteration it + 1 are issued once iteration it's loaded values
   // are unpacked, before it is computed (one register buffer).
   // Loads are unconditional (a chunk past s_valid, or under the causal
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
   auto load_rows = [&](uint4 (&x)[RPI][CH], uint4 (&y)[RPI][CH], int it) {
 #pragma unroll
     for (int u = 0; u < RPI; ++u) {
-      const int i = qb * R + wave + 4 * (it * RPI + u);
+      const int i = qb * R + wave + NW * (it * RPI + u);
       const int last = d.causal ? min(s_valid - V, i / V * V) : s_valid - V;
 #pragma unroll
       for (int t = 0; t < CH; ++t) {
@@ -201,7 +201,7 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
     const int hi = 64 * (t + 1) * V;
     return hi <= s_valid && (!d.causal || hi - 1 <= i);
   };
-  const int n_it = R / (4 * RPI);
+  const int n_it = R / (NW * RPI);
   // With PF an iteration's stores (the output chunks and, for R = 128, the
   // row checksum pairs) are issued in the next iteration, after its wait:
   // the compiler's wait for loaded data also drains every store in flight,
@@ -212,7 +212,7 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
   auto flush = [&](int it) {
 #pragma unroll
     for (int u = 0; u < RPI; ++u) {
-      const int i = qb * R + wave + 4 * (it * RPI + u);
+      const int i = qb * R + wave + NW * (it * RPI + u);
 #pragma unroll
       for (int t = 0; t < CH; ++t) {
         if (64 * t * V >= s_valid) continue;
@@ -258,7 +258,7 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
     }
 #pragma unroll
     for (int u = 0; u < RPI; ++u) {
-      const int rl = wave + 4 * (it * RPI + u);
+      const int rl = wave + NW * (it * RPI + u);
       const int i = qb * R + rl;
       float* const rc_row = d.row_chk + (int64_t(z) * S + i) * nq * 2;  // [S / R][2] of row i
       float (&x)[CH][V] = xs[u];
@@ -423,12 +423,12 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
   }
   if constexpr (PF) flush(n_it - 1);
 
-  // combine the four waves' column checksums in a fixed order: each wave's
-  // partials go to a slab of its own, then every thread sums the four
-  // slabs for its columns
+  // combine the waves' column checksums in a fixed order: each wave's
+  // partials go to a slab of its own, then every thread sums the slabs for
+  // its columns
   if (CHK && d.col_chk != nullptr) {
-    float* p1 = colacc;          // [4][S]
-    float* p2 = colacc + 4 * S;  // [4][S]
+    float* p1 = colacc;           // [NW][S]
+    float* p2 = colacc + NW * S;  // [NW][S]
 #pragma unroll
     for (int t = 0; t < CH; ++t)
 #pragma unroll
@@ -442,8 +442,14 @@ __global__ __launch_bounds__(NT) void softmax_kernel(SoftmaxDesc d) {
     __syncthreads();
     float* cc = d.col_chk + (int64_t(z) * nq + qb) * 2 * S;
     for (int j = tid; j < s_valid; j += NT) {
-      cc[j] = ((p1[j] + p1[S + j]) + p1[2 * S + j]) + p1[3 * S + j];
-      cc[S + j] = ((p2[j] + p2[S + j]) + p2[2 * S + j]) + p2[3 * S + j];
+      float a1 = p1[j], a2 = p2[j];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) {
+        a1 += p1[w * S + j];
+        a2 += p2[w * S + j];
+      }
+      cc[j] = a1;
+      cc[S + j] = a2;
     }
   }
 }
@@ -464,6 +470,40 @@ int xcd_cus() {
   return v > 0 ? v : 0;
 }
 
+template <class T, int CH, bool BWD, int NW>
+hipError_t launch_waves(const SoftmaxDesc& d, bool chk, unsigned grid, hipStream_t s) {
+  constexpr int RPI = CH == 1 ? 2 : 1;
+  const size_t lds = size_t(d.S) * 2 * NW * sizeof(float);
+  auto k = chk ? softmax_kernel<T, CH, BWD, RPI, (CH <= 2), true, NW>
+               : softmax_kernel<T, CH, BWD, RPI, (CH <= 2), false, NW>;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k, dim3(grid), dim3(64 * NW), lds, s, d);
+  return hipGetLastError();
+}
+
+// Waves per workgroup. A wave walks its rows one after another (about 0.7 us
+// each with checksums), so a grid that leaves CUs idle splits a query block
+// over more waves, as many as keep the whole grid resident (128 registers a
+// lane: 16 waves per CU; the waves' column slabs in LDS): B2 S512 12 heads
+// fp32, 96 workgroups, 48 us with 4 waves, 22 with 16. A full grid
+// measured no faster with 8 waves than with 4.
+template <class T, int CH, bool BWD>
+hipError_t launch_ch(const SoftmaxDesc& d, bool chk, hipStream_t s) {
+  const unsigned grid = unsigned((d.S / d.R) * d.B * d.nh);
+  if constexpr (CH <= 2) {  // (the longer rows' registers do not fit 128)
+    constexpr int RPI = CH == 1 ? 2 : 1;
+    auto fits = [&](int nw, unsigned per_cu) {
+      return grid <= 256 * per_cu && d.R % (nw * RPI) == 0 &&
+             size_t(d.S) * 2 * nw * sizeof(float) * per_cu <= 144 * 1024;
+    };
+    if (fits(16, 1)) return launch_waves<T, CH, BWD, 16>(d, chk, grid, s);
+    if (fits(8, 2)) return launch_waves<T, CH, BWD, 8>(d, chk, grid, s);
+  }
+  return launch_waves<T, CH, BWD, 4>(d, chk, grid, s);
+}
+
 template <bool BWD>
 hipError_t launch_sm(const SoftmaxDesc& desc, int dtype, hipStream_t s) {
   SoftmaxDesc d = desc;
@@ -474,19 +514,9 @@ hipError_t launch_sm(const SoftmaxDesc& desc, int dtype, hipStream_t s) {
   if ((d.R & (d.R - 1)) != 0 || d.R > 128 || d.R < (dtype == ABFT_FP32 ? 16 : 32))
     return hipErrorInvalidValue;
   const int ch = (d.S + 64 * V - 1) / (64 * V);
-  dim3 grid(unsigned((d.S / d.R) * d.B * d.nh));
-  const size_t lds = size_t(d.S) * 8 * sizeof(float);
   const bool chk = d.col_chk != nullptr || d.row_chk != nullptr;
-#define SM_CASE(TT, CHV)                                                                      \
-  if (ch <= CHV) {                                                                            \
-    auto k = chk ? softmax_kernel<TT, CHV, BWD, (CHV == 1 ? 2 : 1), (CHV <= 2), true>         \
-                 : softmax_kernel<TT, CHV, BWD, (CHV == 1 ? 2 : 1), (CHV <= 2), false>;       \
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),                       \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds)); \
-    if (e != hipSuccess) return e;                                                            \
-    hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, d);                                         \
-    return hipGetLastError();                                                                 \
-  }
+#define SM_CASE(TT, CHV) \
+  if (ch <= CHV) return launch_ch<TT, CHV, BWD>(d, chk, s);
   if (dtype == ABFT_FP32) {
     SM_CASE(float, 1) SM_CASE(float, 2) SM_CASE(float, 4) SM_CASE(float, 8) SM_CASE(float, 16)
   } else {

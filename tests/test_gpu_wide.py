@@ -111,3 +111,63 @@ def test_wide_products_without_root_check():
     rms = clean.float().pow(2).mean().sqrt().item()
     assert abs(O[0, 130, 6].item() - clean[0, 130, 6].item()) <= 128 * U * 4 * rms
     assert abs(O[0, S - 1, 5].item() - clean[0, S - 1, 5].item()) <= 3e4 * U
+
+
+# batch, seq, hidden, heads, R, dtype: fp32 tiles of 32, 64 and 128 columns,
+# and softmax workgroups of 16, 8 and 4 waves (at most 256, 512 and more query
+# blocks; R = 16 and 32 leave few rows for a wave)
+@pytest.mark.parametrize("shape", [(2, 512, 512, 8, 128, "f32"), (1, 352, 128, 1, 32, "f32"),
+                                   (1, 272, 192, 3, 16, "f32"), (4, 512, 1024, 8, 64, "f32"),
+                                   (3, 864, 320, 5, 32, "bf16"), (2, 448, 128, 2, 64, "bf16"),
+                                   (4, 512, 768, 12, 32, "bf16")],
+                         ids=lambda s: "B%d-S%d-H%d-%dh-R%d-%s" % s)
+def test_materialised_stages(shape):
+    """Products of fp32 operands, and the softmax with its checksums, each
+    against the stored tensors it reads."""
+    from paper_2410_11720_amd import abft
+    B, S, H, nh, R, dtype = shape
+    d = H // nh
+    cfg = abft.LayerConfig(B, S, H, nh, dtype=dtype, causal=True, block_rows=R)
+    layer = abft.ProtectedAttention(cfg, capacity=256)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    tdt = cfg.torch_dtype
+
+    def rand(*s, std=1.0):
+        return (torch.randn(*s, generator=gen, device="cuda") * std).to(tdt)
+    X, W, Wo, dO = rand(B, S, H), rand(H, 3 * H, std=0.02), rand(H, H, std=0.02), rand(B, S, H)
+    last = [(op, B - 1, nh - 1, S - 1, d - 1) for op in ("V", "CL")] + [("AS", 0, 0, S - 1, S - 1)]
+    f = abft.faults_to_device([t + (float("inf"),) for t in last])
+    O = layer.forward(X, W, Wo, f)
+    ev = abft.read_report(layer.report)["events"]
+    assert sorted(ev) == sorted(t + ("INF", "RECOMPUTE") for t in last)
+    AS, AP = layer.tensor("AS").double().clone(), layer.tensor("AP").double()
+    APc, APr = layer.tensor("APc").double(), layer.tensor("APr").double()
+    live = torch.ones(S, S, dtype=torch.bool, device="cuda").tril()
+    ref = torch.softmax(AS.masked_fill(~live, float("-inf")) / d ** 0.5, -1)
+    AP = torch.where(live, AP, torch.zeros_like(AP))  # masked pairs: unspecified past the tile
+    # exp2 and the row sum in fp32: a few units of the argument's rounding
+    tol = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -18
+    assert ((AP - ref).abs() <= tol * ref + 1e-7).all()
+    w = torch.arange(1, R + 1, device="cuda", dtype=torch.float64)
+    blocks = AP.view(B, nh, S // R, R, S)
+    eps = 2.0 ** -20 * R
+    allowed = live.view(S // R, R, S).any(1)  # columns some query of the block may see
+    for got, want in ((APc[..., 0, :], blocks.sum(3)), (APc[..., 1, :], (blocks * w.view(R, 1)).sum(3))):
+        err = ((got - want).abs() - eps * (want.abs() + 1e-3))[:, :, allowed]
+        assert (err <= 0).all()
+    cols = AP.view(B, nh, S, S // R, R)
+    reach = live.view(S, S // R, R).any(2)
+    for got, want in ((APr[..., 0], cols.sum(4)), (APr[..., 1], (cols * w).sum(4))):
+        err = ((got - want).abs() - eps * (want.abs() + 1e-3))[:, :, reach]
+        assert (err <= 0).all()
+    dX, dW, dWo = layer.backward(dO, X, W, Wo)
+    assert abft.read_report(layer.report_bwd)["n_events"] == 0
+    if dtype == "f32":
+        x2, g2 = X.view(-1, H), dO.view(-1, H)
+        dcl, dqkv = layer.tensor("dCL").view(-1, H), layer.tensor("dQKV").view(-1, 3 * H)
+        _close("QKV", layer.tensor("QKV").view(-1, 3 * H), x2, W)
+        _close("O", O.view(-1, H), layer.tensor("CL").view(-1, H), Wo)
+        _close("dCL", dcl, g2, Wo.t().contiguous())
+        _close("dWo", dWo, layer.tensor("CL").view(-1, H).t().contiguous(), g2)
+        _close("dWqkv", dW, x2.t().contiguous(), dqkv)
+        _close("dX", dX.view(-1, H), dqkv, W.t().contiguous())
