@@ -71,6 +71,41 @@ __device__ __forceinline__ bf16x8 tr_join(TrPair& t) {
   return __builtin_bit_cast(bf16x8, v);
 }
 
+// Buffer descriptors and copies through them. The copy is in assembly so that
+// the compiler does not count it: it would wait for every copy in flight
+// before a transposing LDS read (and so run a two-stage pipeline as one
+// stage); the kernels wait for a stage's copies themselves. Offsets are 32
+// bits: a lane part that is computed once and a scalar part, against a
+// 64-bit address per lane and copy (100 vector instructions a tile in the
+// fused forward at head dim 128).
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) char lds_char;
+
+__device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// Descriptor of `bytes` bytes at p: loads past them return zero.
+__device__ __forceinline__ u32x4 rsrc_of(const void* p, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  return u32x4{uni(uint32_t(a)), uni(uint32_t(a >> 32) & 0xffffu), uni(bytes), 0x00020000u};
+}
+// Address of an LDS location as the copies take it.
+__device__ __forceinline__ uint32_t lds_addr(const char* p) {
+  return uni(uint32_t(uintptr_t((lds_char*)p)));
+}
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"  // m0 is set and used within the statement
+// 16 bytes per lane from the buffer to LDS [lds, lds + 1024) in lane order.
+__device__ __forceinline__ void dma16(const u32x4& rs, uint32_t lds, uint32_t voff, uint32_t soff) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rs), "s"(soff)
+               : "memory", "m0");
+#endif
+}
+#pragma clang diagnostic pop
+
 template <bool KMAJ, int ROWS, int NT = 256>
 struct Direct {
   static constexpr int BK = 64;
@@ -121,6 +156,28 @@ struct Direct {
         src = base + int64_t(min(k0 + kr, kend - 1)) * ld + min(row0 + c * 8, nrows - 8);
       }
       __builtin_amdgcn_global_load_lds(src, (lds_void*)(st + i * 1024), 16, 0, 0);
+    }
+  }
+
+  // The same copy through a descriptor (all rows inside it): the lane's byte
+  // offset for rows of ldb bytes, and the copy of the image at byte0 (its
+  // first row and k).
+  static constexpr int RUN = KMAJ ? 8 : 64 / (ROWS / 8);  // rows (k rows) per 1-KB run
+  __device__ static __forceinline__ uint32_t voff(uint32_t ldb, int lane) {
+    if constexpr (KMAJ) {
+      return (lane >> 3) * ldb + (((lane & 7) ^ (lane >> 3)) << 4);
+    } else {
+      static_assert(RUN % 4 == 0, "the swizzle repeats in every run");
+      constexpr int CPR = ROWS / 8;
+      return (lane / CPR) * ldb + (((lane % CPR) ^ (2 * ((lane / CPR) & 3))) << 4);
+    }
+  }
+  __device__ static __forceinline__ void issue_buf(const u32x4& rs, uint32_t vo, uint32_t ldb,
+                                                   uint32_t byte0, uint32_t lds, int wave) {
+#pragma unroll
+    for (int j = 0; j < PER_WAVE; ++j) {
+      const int i = wave * PER_WAVE + j;
+      dma16(rs, lds + i * 1024, vo, byte0 + uint32_t(i * RUN) * ldb);
     }
   }
 

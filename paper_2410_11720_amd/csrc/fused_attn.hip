@@ -343,6 +343,10 @@ struct FusedAttn {
   using DV = Direct<false, D, NTH>;    // V image [64 keys][D dims], swizzled
   static constexpr int K_BYTES = KH * DK::BYTES;
   static constexpr int V_BYTES = 2 * DV::BYTES;
+  // tile copies through a buffer descriptor (B8 S1024 12x64: 49.8 -> 48.8 us,
+  // unprotected 31.2 -> 30.4); the protected kernel at head dim 128 measured
+  // 1-2% faster with the compiler's own copies
+  static constexpr bool BUF = D == 64 || !PROT;
   static constexpr int KCL = D + 8;    // K^c strip row (elements), padded
   static constexpr int KC_BYTES = PROT ? 16 * KCL * 2 : 0;
   static constexpr int VR_BYTES = PROT ? FT * 16 * 2 : 0;
@@ -392,7 +396,11 @@ struct FusedAttn {
     const bf16_t* base = static_cast<const bf16_t*>(arg->qkv) + int64_t(b) * S * ld;
     const bf16_t* Qp = base + h * D;
     const bf16_t* Kp = base + H + h * D;
-    const bf16_t* Vp = base + 2 * H + h * D;
+    // this batch element's rows as a copy source (3 H columns: Q | K | V)
+    const uint32_t ldb = 6u * uint32_t(H);
+    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
+    const uint32_t vk = DK::voff(ldb, lane), vv = DV::voff(ldb, lane);
+    const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int nkt = arg->causal ? qt + 1 : nqt;
     const int R = arg->R, NB = FT / R;                  // checksum blocks per key tile
     const int lg_jpb = __builtin_ctz(R / 16);         // 16-key groups per block (log2)
@@ -414,13 +422,26 @@ struct FusedAttn {
     float kcv[4] = {0.f, 0.f, 0.f, 0.f};
     float vrv = 0.f;
     auto issue = [&](int kt, int st) {
-      char* sb = smem + st * STAGE_BYTES;
+      const uint32_t sl = lds0 + uint32_t(st) * STAGE_BYTES;
       const int key0 = kt * FT;
+      if constexpr (!BUF) {
+        char* sb = smem + st * STAGE_BYTES;
+        const bf16_t* Vp = base + 2 * H + h * D;
 #pragma unroll
-      for (int hf = 0; hf < KH; ++hf) DK::issue(Kp, ld, key0, S, hf * 64, sb + hf * DK::BYTES, wave, lane);
+        for (int hf = 0; hf < KH; ++hf)
+          DK::issue(Kp, ld, key0, S, hf * 64, sb + hf * DK::BYTES, wave, lane);
 #pragma unroll
-      for (int im = 0; im < 2; ++im)
-        DV::issue(Vp, ld, 0, D, key0 + 64 * im, sb + K_BYTES + im * DV::BYTES, wave, lane);
+        for (int im = 0; im < 2; ++im)
+          DV::issue(Vp, ld, 0, D, key0 + 64 * im, sb + K_BYTES + im * DV::BYTES, wave, lane);
+      }
+#pragma unroll
+      for (int hf = 0; hf < (BUF ? KH : 0); ++hf)
+        DK::issue_buf(rs, vk, ldb, uint32_t(key0) * ldb + 2u * (H + h * D + hf * 64),
+                      sl + hf * DK::BYTES, wu);
+#pragma unroll
+      for (int im = 0; im < (BUF ? 2 : 0); ++im)
+        DV::issue_buf(rs, vv, ldb, uint32_t(key0 + 64 * im) * ldb + 2u * (2 * H + h * D),
+                      sl + K_BYTES + im * DV::BYTES, wu);
       if constexpr (PROT) {
         if (arg->check_as) {
           const int nqR = S / R;
@@ -1001,14 +1022,14 @@ struct BwdTile {
   // entities cbase + 0..15, rows rbase + 0..127 (see score_locate for A, Bm
   // and tr). A flagged vector is gathered into the wave's scratch and fixed
   // by lane 0; the fixed element is put back into the tile.
-  template <bool TR>
+  template <bool TR, bool MSUM>
   __device__ static void check(floatx4 (&t)[8], const floatx4& cs, const FusedBwdDesc& fd, int op,
                                int b, int h, int cbase, int rbase, const bf16_t* A,
                                const bf16_t* Bm, int64_t lda, int64_t ldb, float* scr, int lane) {
     const int lq = lane & 15, g = lane >> 4;
     const int R = fd.R, NB = FT / R, lg_jpb = __builtin_ctz(R / 16);
     float mine1 = 0.f, minea = 0.f;
-    if constexpr (D == 64) {
+    if constexpr (MSUM) {
       // Each column's sums over the rows of every R-row block on the matrix
       // cores: the values and their magnitudes packed to bf16 (a rounding of
       // 2^-9 relative, far inside the detection bound E) as the B operand,
@@ -1032,8 +1053,8 @@ struct BwdTile {
       mine1 = vs[0];
       minea = as[0];
     } else {
-      // the same sums on the vector ALUs (head dim 128: the matrix-core
-      // form holds registers the key pass does not have)
+      // the same sums on the vector ALUs (the key pass at head dim 128: the
+      // matrix-core form holds registers it does not have)
       float sj[8], aj[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -1276,23 +1297,28 @@ struct BwdTile {
   }
 };
 
-// The query pass. LDS: per key tile a stage of the K and V images and the
-// K^c, V^c and K^r strips (two stages at head dim 64: the next tile loads
-// while this one is used), the workgroup's Q and dCL images (loaded once),
-// scratch.
+// The query pass. LDS: two stages of a key tile's K and V images and K^c,
+// V^c and K^r strips (the next tile loads while this one is used), scratch,
+// and at head dim 64 the workgroup's Q and dCL images (loaded once). At head
+// dim 128 the two stages leave no room for those: each wave holds its 16
+// queries' fragments in 32 registers. (One stage, the images in LDS: every
+// tile waited for its loads, 9 us a tile even on an idle GPU; B4 S2048 H4096
+// 32x128 614 -> 537 us, and with head dim 64's elementwise code and checks on
+// the matrix cores, which the registers then allowed, 373.)
 template <int D, bool CHK>
 struct FusedBwdQ : BwdTile<D> {
   using T = BwdTile<D>;
   using typename T::DK;
   static constexpr int KS = T::KS, DB = T::DB, KH = T::KH, IMG = T::IMG, SCL = T::SCL;
-  static constexpr int NBUF = D == 64 ? 2 : 1;
+  static constexpr int NBUF = 2;
+  static constexpr bool REGS = D == 128;  // Q and dCL fragments in registers
   // offsets within a stage
   static constexpr int OFF_V = IMG, OFF_KC = 2 * IMG, OFF_VC = OFF_KC + T::STRIP;
   static constexpr int OFF_KR = OFF_VC + T::STRIP;
   static constexpr int STAGE = T::align1k(OFF_KR + T::RSTRIP);
   static constexpr int OFF_ZERO = NBUF * STAGE;
   static constexpr int OFF_Q = T::align1k(OFF_ZERO + T::ZERO), OFF_G = OFF_Q + IMG;
-  static constexpr int OFF_SCR = OFF_G + IMG;
+  static constexpr int OFF_SCR = REGS ? OFF_Q : OFF_G + IMG;
   static constexpr int LDS_BYTES = OFF_SCR + (BNT / 64) * T::SCR * 4;
   static_assert(LDS_BYTES <= 160 * 1024, "one workgroup fits the LDS");
 
@@ -1312,6 +1338,11 @@ struct FusedBwdQ : BwdTile<D> {
     const bf16_t* Vp = base + 2 * H + h * D;
     const bf16_t* dCLp = static_cast<const bf16_t*>(fd.dcl) + int64_t(b) * S * H + h * D;
     const bf16_t* CLp = static_cast<const bf16_t*>(fd.cl) + int64_t(b) * S * H + h * D;
+    // this batch element's rows as copy sources
+    const uint32_t ldb = 6u * uint32_t(H), ldg = 2u * uint32_t(H);
+    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
+    const uint32_t vo = DK::voff(ldb, lane);
+    const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int nkt = fd.causal ? qt + 1 : nqt;
     const float sl2 = fd.scale * 1.4426950408889634f;
     constexpr bool chk = CHK;
@@ -1339,11 +1370,26 @@ struct FusedBwdQ : BwdTile<D> {
       sdq = fd.scale * dq;       // dS = P (scale dP - scale D)
       if (g == 0) fd.drow[(int64_t(b) * fd.nh + h) * S + q] = dq;
     }
-    // Q and dCL images of the workgroup's queries (complete with tile 0)
+    // Q and dCL of the workgroup's queries: images (complete with tile 0), or
+    // the wave's B operand fragments (query q, dims 32 kk + 8 g..)
+    bf16x8 qreg[REGS ? KS : 1], greg[REGS ? KS : 1];
+    if constexpr (REGS) {
 #pragma unroll
-    for (int hf = 0; hf < KH; ++hf) {
-      DK::issue(Qp, ld, q0, S, hf * 64, smem + OFF_Q + hf * DK::BYTES, wave, lane);
-      DK::issue(dCLp, H, q0, S, hf * 64, smem + OFF_G + hf * DK::BYTES, wave, lane);
+      for (int kk = 0; kk < KS; ++kk) {
+        qreg[kk] = *reinterpret_cast<const bf16x8*>(Qp + int64_t(q) * ld + 32 * kk + 8 * g);
+        greg[kk] = *reinterpret_cast<const bf16x8*>(dCLp + int64_t(q) * H + 32 * kk + 8 * g);
+      }
+    }
+    if constexpr (!REGS) {
+      const u32x4 rg = rsrc_of(dCLp - h * D, uint32_t(S) * ldg);
+      const uint32_t vg = DK::voff(ldg, lane);
+#pragma unroll
+      for (int hf = 0; hf < KH; ++hf) {
+        DK::issue_buf(rs, vo, ldb, uint32_t(q0) * ldb + 2u * (h * D + hf * 64),
+                      lds0 + OFF_Q + hf * DK::BYTES, wu);
+        DK::issue_buf(rg, vg, ldg, uint32_t(q0) * ldg + 2u * (h * D + hf * 64),
+                      lds0 + OFF_G + hf * DK::BYTES, wu);
+      }
     }
     const bf16_t* zeros = reinterpret_cast<const bf16_t*>(smem + OFF_ZERO);
     if (chk && tid < T::ZERO / 4) reinterpret_cast<uint32_t*>(smem + OFF_ZERO)[tid] = 0u;
@@ -1352,7 +1398,7 @@ struct FusedBwdQ : BwdTile<D> {
     // copies, the strips' values into registers (written by commit)
     float kcv[T::NSV], vcv[T::NSV];
     bf16x8 krv[T::CPP];
-    auto issue = [&](int kt, int st) {
+    auto issue_values = [&](int kt) {
       const int key0 = kt * FT;
       if (chk) {
         const int64_t blk0 = int64_t(b) * nqR + key0 / R;
@@ -1360,11 +1406,14 @@ struct FusedBwdQ : BwdTile<D> {
         T::strip_issue(fd.qkvc + 2 * H + h * D, ld, blk0, NB, tid, vcv);
         T::rstrip_issue(Kp, ld, key0, S, tid, krv);
       }
-      char* sb = smem + st * STAGE;
+    };
+    auto issue_copies = [&](int kt, int st) {
+      const uint32_t sl = lds0 + uint32_t(st) * STAGE, row = uint32_t(kt * FT) * ldb;
 #pragma unroll
       for (int hf = 0; hf < KH; ++hf) {
-        DK::issue(Kp, ld, key0, S, hf * 64, sb + hf * DK::BYTES, wave, lane);
-        DK::issue(Vp, ld, key0, S, hf * 64, sb + OFF_V + hf * DK::BYTES, wave, lane);
+        DK::issue_buf(rs, vo, ldb, row + 2u * (H + h * D + hf * 64), sl + hf * DK::BYTES, wu);
+        DK::issue_buf(rs, vo, ldb, row + 2u * (2 * H + h * D + hf * 64),
+                      sl + OFF_V + hf * DK::BYTES, wu);
       }
     };
     auto commit = [&](int st) {
@@ -1382,25 +1431,22 @@ struct FusedBwdQ : BwdTile<D> {
     float* scr = reinterpret_cast<float*>(smem + OFF_SCR) + wave * T::SCR;
     // B operand fragment of the wave's queries (rows of the Q or dCL image)
     auto bfrag = [&](int off, int kk) {
-      return DK::frag(smem + off + (kk >> 1) * DK::BYTES, wave * 16, (kk & 1) * 32, lane);
+      if constexpr (REGS) return off == OFF_Q ? qreg[kk] : greg[kk];
+      else return DK::frag(smem + off + (kk >> 1) * DK::BYTES, wave * 16, (kk & 1) * 32, lane);
     };
 
-    if (NBUF == 2) {
-      issue(0, 0);
-      wait_vmcnt<0>();
-      commit(0);
-    }
+    issue_values(0);
+    issue_copies(0, 0);
+    wait_vmcnt<0>();
+    commit(0);
     for (int kt = 0; kt < nkt; ++kt) {
-      const int st = NBUF == 2 ? (kt & 1) : 0;
-      if (NBUF == 1) {
-        issue(kt, 0);
-        wait_vmcnt<0>();
-        commit(0);
-      }
-      // tile kt in LDS (double-buffered: the other stage is free)
+      const int st = kt & 1;
+      // tile kt in LDS; the other stage is free
       __syncthreads();
-      const bool pre = NBUF == 2 && kt + 1 < nkt;
-      if (pre) issue(kt + 1, st ^ 1);
+      const bool pre = kt + 1 < nkt;
+      // (head dim 128: the strips' values later, for registers)
+      if (pre && !REGS) issue_values(kt + 1);
+      if (pre) issue_copies(kt + 1, st ^ 1);
       const char* sb = smem + st * STAGE;
       const bf16_t* krs = reinterpret_cast<const bf16_t*>(sb + OFF_KR);
       const int key0 = kt * FT;
@@ -1428,7 +1474,7 @@ struct FusedBwdQ : BwdTile<D> {
         }
         if (wf) T::template inject<false>(s, fd, ABFT_OP_AS, b, h, qw, key0, lane);
         if (chk)
-          T::template check<false>(s, ks, fd, ABFT_OP_AS, b, h, qw, key0, Qp, Kp, ld, ld, scr, lane);
+          T::template check<false, true>(s, ks, fd, ABFT_OP_AS, b, h, qw, key0, Qp, Kp, ld, ld, scr, lane);
         // masked keys (diagonal tile only) enter the exponential as -inf
         auto probs = [&](auto masked) {
 #pragma unroll
@@ -1442,25 +1488,10 @@ struct FusedBwdQ : BwdTile<D> {
             pk[j] = T::pack4v(a);
           }
         };
-        // (head dim 64: a copy without the mask for the other tiles; head
-        // dim 128: one copy, per element, as its registers allow)
-        if constexpr (D == 64) {
-          if (diag)
-            probs(std::true_type{});
-          else
-            probs(std::false_type{});
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            float a[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const bool live = !(diag && key0 + 16 * j + 4 * g + r > q);
-              a[r] = live ? bf2f(f2bf(__builtin_amdgcn_exp2f(s[j][r] * sl2 - mq) * il)) : 0.f;
-            }
-            pk[j] = T::pack4(a);
-          }
-        }
+        if (diag)
+          probs(std::true_type{});
+        else
+          probs(std::false_type{});
       }
       {
         // dP^T = V dCL^T with its strip rows, checked; dS from P and dP
@@ -1483,7 +1514,7 @@ struct FusedBwdQ : BwdTile<D> {
         }
         if (wf) T::template inject<false>(dp, fd, ABFT_OP_DAP, b, h, qw, key0, lane);
         if (chk)
-          T::template check<false>(dp, vs, fd, ABFT_OP_DAP, b, h, qw, key0, dCLp, Vp, H, ld, scr,
+          T::template check<false, true>(dp, vs, fd, ABFT_OP_DAP, b, h, qw, key0, dCLp, Vp, H, ld, scr,
                                    lane);
         auto grads = [&](auto masked) {
 #pragma unroll
@@ -1498,29 +1529,14 @@ struct FusedBwdQ : BwdTile<D> {
             pk[j] = T::pack4v(ds);
           }
         };
-        // (head dim 64: a copy without the mask for the other tiles; head
-        // dim 128: one copy, per element, as its registers allow)
-        if constexpr (D == 64) {
-          if (diag)
-            grads(std::true_type{});
-          else
-            grads(std::false_type{});
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            float a[4], ds[4];
-            T::unpack4(pk[j], a);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const bool live = !(diag && key0 + 16 * j + 4 * g + r > q);
-              ds[r] = live ? bf2f(f2bf(fd.scale * a[r] * (dp[j][r] - dq))) : 0.f;
-            }
-            pk[j] = T::pack4(ds);
-          }
-        }
+        if (diag)
+          grads(std::true_type{});
+        else
+          grads(std::false_type{});
       }
       // the next tile's strips into the free stage
-      if (pre) commit(st ^ 1);
+      if (pre && REGS) issue_values(kt + 1);
+      if (pre && !REGS) commit(st ^ 1);
       // dQ^T += K^T dS^T and (dQ^r)^T += (K^r)^T dS^T
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
@@ -1533,10 +1549,8 @@ struct FusedBwdQ : BwdTile<D> {
           kra = __builtin_amdgcn_mfma_f32_16x16x32_bf16(T::rs_frag(krs, zeros, 32 * t, lane), pf,
                                                         kra, 0, 0, 0);
       }
-      if (NBUF == 2)
-        wait_vmcnt<0>();  // the next tile's copies
-      else
-        __syncthreads();  // the one stage is reloaded next
+      if (pre && REGS) commit(st ^ 1);
+      wait_vmcnt<0>();  // the next tile's copies
     }
 
     bf16_t* dQp = static_cast<bf16_t*>(fd.dqkv) + int64_t(b) * S * fd.ld + h * D;
@@ -1546,9 +1560,13 @@ struct FusedBwdQ : BwdTile<D> {
 
 // The key pass. LDS: the workgroup's K and V images (loaded once); per
 // query tile a stage of the Q and dCL images, the Q^c and dCL^c strips,
-// the Q^r and dCL^r row-checksum strips and the queries' max, 1 / sum and D
-// (two stages at head dim 64: the next tile loads while this one is used);
-// scratch.
+// the Q^r and dCL^r row-checksum strips and the queries' max + log2 of the
+// sum and D (two stages at head dim 64, and in PART 1 at head dim 128, whose
+// K fragments are in registers: the next tile loads while this one is used);
+// scratch. Bound by vector ALU work; at head dim 128 P and dS took about 16
+// instructions an element in a masked, twice rounded form, now four (the mask
+// in a copy of its own): B4 S2048 H4096 32x128 1090 -> 850 us, with PART 1's
+// two stages and matrix-core checks 760; unprotected 627 -> 517.
 // PART 0 forms dV and dK together; where both sets of accumulators do not
 // fit the registers of two waves per SIMD (head dim 128) the pass runs as
 // PART 1 (S, P, dV) then PART 2 (S, P, dP, dS, dK), each recomputing and
@@ -1559,14 +1577,20 @@ struct FusedBwdKV : BwdTile<D> {
   using T = BwdTile<D>;
   using typename T::DK;
   static constexpr int KS = T::KS, DB = T::DB, KH = T::KH, IMG = T::IMG, SCL = T::SCL;
-  static constexpr int NBUF = D == 64 ? 2 : 1;
-  static constexpr int OFF_V = IMG, OFF_ST = 2 * IMG;
+  // query tile copies through a buffer descriptor: without checks at head
+  // dim 128 (B4 S2048 32x128: 567 -> 517 us); the other forms measured 2-6%
+  // slower with it (B8 S1024 12x64 protected 75 -> 80 us)
+  static constexpr bool BUF = D == 128 && PART == 0;
+  // K fragments of the wave's keys in registers, no image (V is not used)
+  static constexpr bool REGS = D == 128 && PART == 1;
+  static constexpr int NBUF = D == 64 || REGS ? 2 : 1;
+  static constexpr int OFF_V = IMG, OFF_ST = REGS ? 0 : 2 * IMG;
   // offsets within a stage
   static constexpr int OFF_Q = 0, OFF_G = IMG;
   static constexpr int OFF_QC = 2 * IMG, OFF_GC = OFF_QC + T::STRIP;
   static constexpr int OFF_QR = OFF_GC + T::STRIP, OFF_GR = OFF_QR + T::RSTRIP;
-  static constexpr int OFF_ROW = OFF_GR + T::RSTRIP;            // [3][128] floats
-  static constexpr int STAGE = T::align1k(OFF_ROW + 3 * FT * 4);
+  static constexpr int OFF_ROW = OFF_GR + T::RSTRIP;            // [2][128] floats
+  static constexpr int STAGE = T::align1k(OFF_ROW + 2 * FT * 4);
   static constexpr int OFF_ZERO = OFF_ST + NBUF * STAGE;
   static constexpr int OFF_SCR = OFF_ZERO + T::ZERO;
   static constexpr int LDS_BYTES = OFF_SCR + (BNT / 64) * T::SCR * 4;
@@ -1587,6 +1611,12 @@ struct FusedBwdKV : BwdTile<D> {
     const bf16_t* Kp = base + H + h * D;
     const bf16_t* Vp = base + 2 * H + h * D;
     const bf16_t* dCLp = static_cast<const bf16_t*>(fd.dcl) + int64_t(b) * S * H + h * D;
+    // this batch element's rows as copy sources
+    const uint32_t ldb = 6u * uint32_t(H), ldg = 2u * uint32_t(H);
+    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
+    const u32x4 rg = rsrc_of(dCLp - h * D, uint32_t(S) * ldg);
+    const uint32_t vo = DK::voff(ldb, lane), vg = DK::voff(ldg, lane);
+    const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int qt0 = fd.causal ? kt : 0;
     const float sl2 = fd.scale * 1.4426950408889634f;
     constexpr bool chk = CHK;
@@ -1598,10 +1628,18 @@ struct FusedBwdKV : BwdTile<D> {
                                   (1u << ABFT_OP_DV));
 
     // K and V images of the workgroup's keys (complete with the first tile)
+    bf16x8 kreg[REGS ? KS : 1];
+    if constexpr (REGS) {
 #pragma unroll
-    for (int hf = 0; hf < KH; ++hf) {
-      DK::issue(Kp, ld, key0, S, hf * 64, smem + hf * DK::BYTES, wave, lane);
-      DK::issue(Vp, ld, key0, S, hf * 64, smem + OFF_V + hf * DK::BYTES, wave, lane);
+      for (int kk = 0; kk < KS; ++kk)
+        kreg[kk] = *reinterpret_cast<const bf16x8*>(Kp + int64_t(key) * ld + 32 * kk + 8 * g);
+    }
+#pragma unroll
+    for (int hf = 0; hf < (REGS ? 0 : KH); ++hf) {
+      DK::issue_buf(rs, vo, ldb, uint32_t(key0) * ldb + 2u * (H + h * D + hf * 64),
+                    lds0 + hf * DK::BYTES, wu);
+      DK::issue_buf(rs, vo, ldb, uint32_t(key0) * ldb + 2u * (2 * H + h * D + hf * 64),
+                    lds0 + OFF_V + hf * DK::BYTES, wu);
     }
     const bf16_t* zeros = reinterpret_cast<const bf16_t*>(smem + OFF_ZERO);
     if (chk && tid < T::ZERO / 4) reinterpret_cast<uint32_t*>(smem + OFF_ZERO)[tid] = 0u;
@@ -1631,25 +1669,31 @@ struct FusedBwdKV : BwdTile<D> {
       }
     };
     auto issue_copies = [&](int qt, int st) {
-      const int q0 = qt * FT;
-      char* sb = smem + OFF_ST + st * STAGE;
+      if constexpr (!BUF) {
+        char* sb = smem + OFF_ST + st * STAGE;
 #pragma unroll
-      for (int hf = 0; hf < KH; ++hf) {
-        DK::issue(Qp, ld, q0, S, hf * 64, sb + OFF_Q + hf * DK::BYTES, wave, lane);
-        DK::issue(dCLp, H, q0, S, hf * 64, sb + OFF_G + hf * DK::BYTES, wave, lane);
+        for (int hf = 0; hf < KH; ++hf) {
+          DK::issue(Qp, ld, qt * FT, S, hf * 64, sb + OFF_Q + hf * DK::BYTES, wave, lane);
+          DK::issue(dCLp, H, qt * FT, S, hf * 64, sb + OFF_G + hf * DK::BYTES, wave, lane);
+        }
+      }
+      const uint32_t sl = lds0 + OFF_ST + uint32_t(st) * STAGE, q0 = uint32_t(qt * FT);
+#pragma unroll
+      for (int hf = 0; hf < (BUF ? KH : 0); ++hf) {
+        DK::issue_buf(rs, vo, ldb, q0 * ldb + 2u * (h * D + hf * 64), sl + OFF_Q + hf * DK::BYTES,
+                      wu);
+        DK::issue_buf(rg, vg, ldg, q0 * ldg + 2u * (h * D + hf * 64), sl + OFF_G + hf * DK::BYTES,
+                      wu);
       }
     };
     auto commit = [&](int st) {
       char* sb = smem + OFF_ST + st * STAGE;
       float* rowf = reinterpret_cast<float*>(sb + OFF_ROW);
       if (tid < FT) {
-        // head dim 64: max + log2(sum), so that P = exp2(scaled score -
-        // that); 128: the max and 1 / sum
-        rowf[tid] = D == 64 ? rv0 + __log2f(rv1) : rv0;
-        rowf[FT + tid] = 1.f / rv1;
+        // max + log2(sum): P = exp2(scaled score - that)
+        rowf[tid] = rv0 + __log2f(rv1);
       } else if (tid < 2 * FT) {
-        // D per query (head dim 64: scale D, for dS = P (scale dP - scale D))
-        rowf[2 * FT + tid - FT] = D == 64 ? fd.scale * rv0 : rv0;
+        rowf[tid] = fd.scale * rv0;  // scale D: dS = P (scale dP - scale D)
       }
       if (chk) {
         T::strip_commit(reinterpret_cast<bf16_t*>(sb + OFF_QC), NB, tid, qcv);
@@ -1672,7 +1716,8 @@ struct FusedBwdKV : BwdTile<D> {
       return DK::frag(img + (kk >> 1) * DK::BYTES, 16 * j, (kk & 1) * 32, lane);
     };
     auto kfrag = [&](int off, int kk) {
-      return DK::frag(smem + off + (kk >> 1) * DK::BYTES, wave * 16, (kk & 1) * 32, lane);
+      if constexpr (REGS) return kreg[kk];
+      else return DK::frag(smem + off + (kk >> 1) * DK::BYTES, wave * 16, (kk & 1) * 32, lane);
     };
 
     if (NBUF == 2) {
@@ -1720,7 +1765,7 @@ struct FusedBwdKV : BwdTile<D> {
         }
         if (DO_K && wf) T::template inject<true>(s, fd, ABFT_OP_AS, b, h, kw, q0, lane);
         if (chk)
-          T::template check<true>(s, cs, fd, ABFT_OP_AS, b, h, kw, q0, Kp, Qp, ld, ld, scr, lane);
+          T::template check<true, D == 64 || PART == 1>(s, cs, fd, ABFT_OP_AS, b, h, kw, q0, Kp, Qp, ld, ld, scr, lane);
         // masked queries (diagonal tile only) enter the exponential as -inf
         auto probs = [&](auto masked) {
 #pragma unroll
@@ -1736,28 +1781,12 @@ struct FusedBwdKV : BwdTile<D> {
             pk[j] = T::pack4v(a);
           }
         };
-        // (head dim 64: a copy without the mask for the other tiles; head
-        // dim 128: one copy, per element, as its registers allow)
-        if constexpr (D == 64) {
-          if (diag)
-            probs(std::true_type{});
-          else
-            probs(std::false_type{});
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float4 m4 = *reinterpret_cast<const float4*>(rowf + 16 * j + 4 * g);
-            const float4 i4 = *reinterpret_cast<const float4*>(rowf + FT + 16 * j + 4 * g);
-            const float mv[4] = {m4.x, m4.y, m4.z, m4.w}, iv[4] = {i4.x, i4.y, i4.z, i4.w};
-            float a[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const bool live = !(diag && key > q0 + 16 * j + 4 * g + r);
-              a[r] = live ? bf2f(f2bf(__builtin_amdgcn_exp2f(s[j][r] * sl2 - mv[r]) * iv[r])) : 0.f;
-            }
-            pk[j] = T::pack4(a);
-          }
-        }
+        if constexpr (D == 128 && PART == 0)
+          probs(diag);
+        else if (diag)
+          probs(std::true_type{});
+        else
+          probs(std::false_type{});
       }
       // the next tile's values, written to the free stage at the end
       if (pre) issue_values(qt + 1);
@@ -1792,12 +1821,12 @@ struct FusedBwdKV : BwdTile<D> {
         }
         if (wf) T::template inject<true>(dp, fd, ABFT_OP_DAP, b, h, kw, q0, lane);
         if (chk)
-          T::template check<true>(dp, cs, fd, ABFT_OP_DAP, b, h, kw, q0, Vp, dCLp, ld, H, scr,
+          T::template check<true, D == 64 || PART == 1>(dp, cs, fd, ABFT_OP_DAP, b, h, kw, q0, Vp, dCLp, ld, H, scr,
                                   lane);
         auto grads = [&](auto masked) {
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
-            const float4 d4 = *reinterpret_cast<const float4*>(rowf + 2 * FT + 16 * j + 4 * g);
+            const float4 d4 = *reinterpret_cast<const float4*>(rowf + FT + 16 * j + 4 * g);
             const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
             float a[4], ds[4];
             T::unpack4(pk[j], a);
@@ -1809,28 +1838,12 @@ struct FusedBwdKV : BwdTile<D> {
             pk[j] = T::pack4v(ds);
           }
         };
-        // (head dim 64: a copy without the mask for the other tiles; head
-        // dim 128: one copy, per element, as its registers allow)
-        if constexpr (D == 64) {
-          if (diag)
-            grads(std::true_type{});
-          else
-            grads(std::false_type{});
-        } else {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const float4 d4 = *reinterpret_cast<const float4*>(rowf + 2 * FT + 16 * j + 4 * g);
-            const float dv[4] = {d4.x, d4.y, d4.z, d4.w};
-            float a[4], ds[4];
-            T::unpack4(pk[j], a);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const bool live = !(diag && key > q0 + 16 * j + 4 * g + r);
-              ds[r] = live ? bf2f(f2bf(fd.scale * a[r] * (dp[j][r] - dv[r]))) : 0.f;
-            }
-            pk[j] = T::pack4(ds);
-          }
-        }
+        if constexpr (D == 128 && PART == 0)
+          grads(diag);
+        else if (diag)
+          grads(std::true_type{});
+        else
+          grads(std::false_type{});
       }
       // dK^T += Q^T dS and (dK^r)^T += (Q^r)^T dS
 #pragma unroll
@@ -1946,13 +1959,10 @@ hipError_t launch_fused_bwd_kv(const FusedBwdDesc& fd, hipStream_t s) {
   if (fd.D == 128 && !fd.check)
     return launch_bwd_kernel<fused_bwd_kv_kernel<128, false, 0>>(fd, FusedBwdKV<128, false, 0>::LDS_BYTES, s);
   if (fd.D == 128) {
-    hipError_t e = fd.check
-        ? launch_bwd_kernel<fused_bwd_kv_kernel<128, true, 1>>(fd, FusedBwdKV<128, true, 1>::LDS_BYTES, s)
-        : launch_bwd_kernel<fused_bwd_kv_kernel<128, false, 1>>(fd, FusedBwdKV<128, false, 1>::LDS_BYTES, s);
+    const hipError_t e =
+        launch_bwd_kernel<fused_bwd_kv_kernel<128, true, 1>>(fd, FusedBwdKV<128, true, 1>::LDS_BYTES, s);
     if (e != hipSuccess) return e;
-    return fd.check
-        ? launch_bwd_kernel<fused_bwd_kv_kernel<128, true, 2>>(fd, FusedBwdKV<128, true, 2>::LDS_BYTES, s)
-        : launch_bwd_kernel<fused_bwd_kv_kernel<128, false, 2>>(fd, FusedBwdKV<128, false, 2>::LDS_BYTES, s);
+    return launch_bwd_kernel<fused_bwd_kv_kernel<128, true, 2>>(fd, FusedBwdKV<128, true, 2>::LDS_BYTES, s);
   }
   return hipErrorInvalidValue;
 }

@@ -19,15 +19,12 @@
 
 #include "abft_internal.hpp"
 #include "abft_device.hpp"
+#include "direct_lds.hpp"
 
 namespace abft {
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef short short8_t __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) char lds_char;
-typedef __attribute__((address_space(3))) short4_t lds_short4;
 
 __device__ __forceinline__ const GemmDesc& wide_desc(int slot) {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -38,30 +35,6 @@ __device__ __forceinline__ const GemmDesc& wide_desc(int slot) {
   return *static_cast<const GemmDesc*>(nullptr);  // the host pass emits no device code
 #endif
 }
-
-__device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
-// Buffer descriptor of `bytes` bytes at p: loads past them return zero.
-__device__ __forceinline__ u32x4 rsrc_of(const void* p, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(p);
-  return u32x4{uni(uint32_t(a)), uni(uint32_t(a >> 32) & 0xffffu), uni(bytes), 0x00020000u};
-}
-
-// 16 bytes per lane from the buffer to LDS [lds, lds + 1024) in lane order.
-// In assembly so that the compiler does not count the copy: it would wait
-// for every one in flight before a transposing LDS read. The kernel waits
-// for a stage's copies itself (wait_vm).
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"  // m0 is set and used within the statement
-__device__ __forceinline__ void dma16(const u32x4& rs, uint32_t lds, uint32_t voff, uint32_t soff) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds), "v"(voff), "s"(rs), "s"(soff)
-               : "memory", "m0");
-#endif
-}
-#pragma clang diagnostic pop
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -220,7 +193,7 @@ struct Wide {
     const u32x4 ra = rsrc_of(g.A, uint32_t(AK ? M : K) * lda);
     const u32x4 rb = rsrc_of(g.B, uint32_t(BKM ? N : K) * ldb);
     const uint32_t va = OA::voff(lda, lane), vb = OB::voff(ldb, lane);
-    const uint32_t lds0 = uint32_t(uintptr_t((lds_char*)smem));
+    const uint32_t lds0 = lds_addr(smem);
     int srun = -1;            // this wave's strip run
     bool srow = false;        // of the row strip
     u32x4 rs = ra;
