@@ -106,13 +106,15 @@ __device__ __forceinline__ void round_chunk(float (&x)[4], uint4& bits) {
 // CH: 16-byte chunks per lane per row (S <= 64 * CH * VEC); RPI rows per
 // iteration per wave; PF: prefetch the next iteration's rows; CHK: encode
 // the checksums (some of col_chk, row_chk given); NW: waves per workgroup
-// (see launch_sm).
-template <class T, int CH, bool BWD, int RPI, bool PF, bool CHK, int NW>
-__global__ __launch_bounds__(64 * NW) void softmax_kernel(SoftmaxDesc d) {
+// (see launch_ch). TURNS: the waves add their column sums to one LDS slab in
+// turn, and keep to the 256 registers of two waves per SIMD.
+template <class T, int CH, bool BWD, int RPI, bool PF, bool CHK, int NW, bool TURNS>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(TURNS ? 2 : 1)))
+void softmax_kernel(SoftmaxDesc d) {
   constexpr int NT = 64 * NW;
   constexpr int V = Vec<T>::N;
   extern __shared__ __align__(16) char smem[];
-  float* colacc = reinterpret_cast<float*>(smem);  // [2 NW][S]
+  float* colacc = reinterpret_cast<float*>(smem);  // [2 NW][S], TURNS: [2][S]
 
   // the wave index is uniform over the wave: row indices and row
   // addresses stay in scalar registers
@@ -426,7 +428,39 @@ __global__ __launch_bounds__(64 * NW) void softmax_kernel(SoftmaxDesc d) {
   // combine the waves' column checksums in a fixed order: each wave's
   // partials go to a slab of its own, then every thread sums the slabs for
   // its columns
-  if (CHK && d.col_chk != nullptr) {
+  if (TURNS && CHK && d.col_chk != nullptr) {
+    float* p1 = colacc;      // [S]
+    float* p2 = colacc + S;  // [S]
+    float* cc = d.col_chk + (int64_t(z) * nq + qb) * 2 * S;
+    for (int w = 0; w < NW; ++w) {
+      if (wave == w) {
+#pragma unroll
+        for (int t = 0; t < CH; ++t)
+#pragma unroll
+          for (int e = 0; e < V; e += 4) {
+            const int j = (lc + 64 * t) * V + e;  // (s_valid is a multiple of V)
+            if (j < s_valid) {
+              float4 a = make_float4(c1[t][e], c1[t][e + 1], c1[t][e + 2], c1[t][e + 3]);
+              float4 b = make_float4(c2[t][e], c2[t][e + 1], c2[t][e + 2], c2[t][e + 3]);
+              if (w > 0) {
+                const float4 x = *reinterpret_cast<const float4*>(p1 + j);
+                const float4 y = *reinterpret_cast<const float4*>(p2 + j);
+                a = make_float4(x.x + a.x, x.y + a.y, x.z + a.z, x.w + a.w);
+                b = make_float4(y.x + b.x, y.y + b.y, y.z + b.z, y.w + b.w);
+              }
+              if (w == NW - 1) {  // the last wave's sums are the totals
+                *reinterpret_cast<float4*>(cc + j) = a;
+                *reinterpret_cast<float4*>(cc + S + j) = b;
+              } else {
+                *reinterpret_cast<float4*>(p1 + j) = a;
+                *reinterpret_cast<float4*>(p2 + j) = b;
+              }
+            }
+          }
+      }
+      if (w + 1 < NW) __syncthreads();
+    }
+  } else if (CHK && d.col_chk != nullptr) {
     float* p1 = colacc;           // [NW][S]
     float* p2 = colacc + NW * S;  // [NW][S]
 #pragma unroll
@@ -470,12 +504,12 @@ int xcd_cus() {
   return v > 0 ? v : 0;
 }
 
-template <class T, int CH, bool BWD, int NW>
+template <class T, int CH, bool BWD, int NW, bool TURNS = false>
 hipError_t launch_waves(const SoftmaxDesc& d, bool chk, unsigned grid, hipStream_t s) {
   constexpr int RPI = CH == 1 ? 2 : 1;
-  const size_t lds = size_t(d.S) * 2 * NW * sizeof(float);
-  auto k = chk ? softmax_kernel<T, CH, BWD, RPI, (CH <= 2), true, NW>
-               : softmax_kernel<T, CH, BWD, RPI, (CH <= 2), false, NW>;
+  const size_t lds = size_t(d.S) * 2 * (TURNS ? 1 : NW) * sizeof(float);
+  auto k = chk ? softmax_kernel<T, CH, BWD, RPI, (CH <= 2), true, NW, TURNS>
+               : softmax_kernel<T, CH, BWD, RPI, (CH <= 2), false, NW, false>;
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
   if (e != hipSuccess) return e;
@@ -501,6 +535,15 @@ hipError_t launch_ch(const SoftmaxDesc& d, bool chk, hipStream_t s) {
     if (fits(16, 1)) return launch_waves<T, CH, BWD, 16>(d, chk, grid, s);
     if (fits(8, 2)) return launch_waves<T, CH, BWD, 8>(d, chk, grid, s);
   }
+  // The longest rows of the forward (S > 2048 bf16): a column slab per wave
+  // is 128 KB at 4096 keys, one workgroup per CU. One slab, added to in turn,
+  // and 256 registers let two share a CU: 40 heads x 4096 causal 533 -> 408
+  // us, 32 x 2560 225 -> 168. That needs blocks to share with: below 1.5 per
+  // CU it loses (9 heads x 4096, 288 blocks, 147 -> 170 us; 384 blocks 185 ->
+  // 182 causal, 286 -> 216 unmasked). The backward's second operand spills at
+  // 256 registers (577 -> 1187 us).
+  if constexpr (CH == 8 && sizeof(T) == 2 && !BWD)
+    if (chk && grid >= 384) return launch_waves<T, CH, BWD, 4, true>(d, chk, grid, s);
   return launch_waves<T, CH, BWD, 4>(d, chk, grid, s);
 }
 

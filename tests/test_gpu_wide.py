@@ -115,11 +115,13 @@ def test_wide_products_without_root_check():
 
 # batch, seq, hidden, heads, R, dtype: fp32 tiles of 32, 64 and 128 columns,
 # and softmax workgroups of 16, 8 and 4 waves (at most 256, 512 and more query
-# blocks; R = 16 and 32 leave few rows for a wave)
+# blocks; R = 16 and 32 leave few rows for a wave); the last two have rows
+# above 2048 keys and at least 384 query blocks (column sums added in turn)
 @pytest.mark.parametrize("shape", [(2, 512, 512, 8, 128, "f32"), (1, 352, 128, 1, 32, "f32"),
                                    (1, 272, 192, 3, 16, "f32"), (4, 512, 1024, 8, 64, "f32"),
                                    (3, 864, 320, 5, 32, "bf16"), (2, 448, 128, 2, 64, "bf16"),
-                                   (4, 512, 768, 12, 32, "bf16")],
+                                   (4, 512, 768, 12, 32, "bf16"), (1, 2176, 1536, 24, 128, "bf16"),
+                                   (1, 2080, 384, 6, 32, "bf16")],
                          ids=lambda s: "B%d-S%d-H%d-%dh-R%d-%s" % s)
 def test_materialised_stages(shape):
     """Products of fp32 operands, and the softmax with its checksums, each
