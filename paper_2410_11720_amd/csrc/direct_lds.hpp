@@ -96,9 +96,14 @@ __device__ __forceinline__ uint32_t lds_addr(const char* p) {
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"  // m0 is set and used within the statement
 // 16 bytes per lane from the buffer to LDS [lds, lds + 1024) in lane order.
+// A vector memory instruction must follow the vector instruction that wrote
+// one of its scalar registers by five wait states. The compiler counts them
+// for its own loads, not for this one, and may reload the descriptor or the
+// offset from a spill lane (v_readlane) right before it: the m0 move and the
+// s_nop make five whatever comes before (m0 itself needs one).
 __device__ __forceinline__ void dma16(const u32x4& rs, uint32_t lds, uint32_t voff, uint32_t soff) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :
                : "s"(lds), "v"(voff), "s"(rs), "s"(soff)
                : "memory", "m0");
