@@ -83,7 +83,8 @@ typedef __attribute__((address_space(3))) char lds_char;
 
 __device__ __forceinline__ uint32_t uni(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
 
-// Descriptor of `bytes` bytes at p: loads past them return zero.
+// Descriptor of `bytes` bytes at p. Copies stay inside it by their own
+// offsets: the range check leaves out the scalar part.
 __device__ __forceinline__ u32x4 rsrc_of(const void* p, uint32_t bytes) {
   const uint64_t a = reinterpret_cast<uint64_t>(p);
   return u32x4{uni(uint32_t(a)), uni(uint32_t(a >> 32) & 0xffffu), uni(bytes), 0x00020000u};

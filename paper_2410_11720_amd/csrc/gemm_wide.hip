@@ -20,6 +20,7 @@
 #include "abft_internal.hpp"
 #include "abft_device.hpp"
 #include "direct_lds.hpp"
+#include "wide_copy.hpp"
 
 namespace abft {
 namespace {
@@ -46,27 +47,13 @@ __device__ __forceinline__ void wg_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// One operand of a workgroup: ROWS rows (of M or N) by 64 of k per stage, as
-// 1-KB runs copied by the NW waves. K-major images are [ROWS][64], 16-byte
-// chunk c of row r at chunk c ^ (r & 7); MN-major ones are 64-column
-// sub-images [64 k][64], chunk c of k-row k at c ^ 2 (k & 3): in both the
-// lanes an LDS read serves together hit different banks.
+// One operand of a workgroup: its runs (WideRuns) shared among the NW waves.
+// In both images the lanes an LDS read serves together hit different banks.
 template <bool KMAJ, int ROWS, int NW>
-struct Opnd {
+struct Opnd : WideRuns<KMAJ> {
   static constexpr int BYTES = ROWS * 128;
   static constexpr int PER = ROWS / 8 / NW;  // runs per wave
   static_assert(ROWS % (8 * NW) == 0, "whole runs per wave");
-
-  __device__ static __forceinline__ uint32_t voff(uint32_t ldb, int lane) {
-    const uint32_t r = lane >> 3, c = lane & 7;
-    return r * ldb + ((KMAJ ? c ^ r : c ^ (2 * (r & 3))) << 4);
-  }
-  // byte offset of run i for k0 = 0
-  __device__ static __forceinline__ uint32_t soff(uint32_t ldb, uint32_t row0, int i) {
-    if constexpr (KMAJ) return (row0 + 8 * i) * ldb;
-    else return uint32_t(8 * (i & 7)) * ldb + (row0 + 64 * (i >> 3)) * 2;
-  }
-  __device__ static __forceinline__ uint32_t kstep(uint32_t ldb) { return KMAJ ? 2u : ldb; }
 };
 
 // K-major fragment (MFMA 16x16x32 operand): row lane % 16 of the 16 at
@@ -192,12 +179,12 @@ struct Wide {
     const uint32_t lda = uint32_t(g.lda) * 2, ldb = uint32_t(g.ldb) * 2;
     const u32x4 ra = rsrc_of(g.A, uint32_t(AK ? M : K) * lda);
     const u32x4 rb = rsrc_of(g.B, uint32_t(BKM ? N : K) * ldb);
-    const uint32_t va = OA::voff(lda, lane), vb = OB::voff(ldb, lane);
+    const uint32_t va = OA::lane_part(lda, lane), vb = OB::lane_part(ldb, lane);
     const uint32_t lds0 = lds_addr(smem);
     int srun = -1;            // this wave's strip run
     bool srow = false;        // of the row strip
     u32x4 rs = ra;
-    uint32_t vs = 0, ss = 0;
+    uint32_t vs = 0;
     if (PROT) {
       const int wc = ((4 * BM >> lg_rm) + 7) / 8;
       const int wr = ROWSTRIP ? ((4 * BN >> lg_rn) + 7) / 8 : 0;
@@ -205,15 +192,14 @@ struct Wide {
         srun = wave;
         const uint32_t ld = uint32_t(g.ldaci) * 2;
         rs = rsrc_of(g.Aci, uint32_t(4 * (M >> lg_rm)) * ld);
-        vs = Opnd<true, 8 * NW, NW>::voff(ld, lane);
-        ss = uint32_t(4 * (m0 >> lg_rm) + 8 * srun) * ld;
+        vs = wide_strip_part(ld, 4 * (m0 >> lg_rm) + 8 * srun, 4 * (M >> lg_rm), lane);
       } else if (wave < wc + wr) {
         srun = wave - wc;
         srow = true;
         const uint32_t ld = uint32_t(g.ldbri) * 2;
-        rs = rsrc_of(g.Bri, uint32_t(4 * ((N - g.cr_n_begin) >> lg_rn)) * ld);
-        vs = Opnd<true, 8 * NW, NW>::voff(ld, lane);
-        ss = uint32_t(4 * ((n0 - g.cr_n_begin) >> lg_rn) + 8 * srun) * ld;
+        const int rows = 4 * ((N - g.cr_n_begin) >> lg_rn);
+        rs = rsrc_of(g.Bri, uint32_t(rows) * ld);
+        vs = wide_strip_part(ld, 4 * ((n0 - g.cr_n_begin) >> lg_rn) + 8 * srun, rows, lane);
       }
     }
     const bool sx = PROT && srun >= 0;
@@ -221,12 +207,12 @@ struct Wide {
     uint32_t sa[OA::PER], sb[OB::PER];
 #pragma unroll
     for (int j = 0; j < OA::PER; ++j)
-      sa[j] = OA::soff(lda, m0, wave * OA::PER + j) + uint32_t(k_lo) * OA::kstep(lda);
+      sa[j] = OA::run_part(lda, m0, M, wave * OA::PER + j) + uint32_t(k_lo) * OA::k_part(lda);
 #pragma unroll
     for (int j = 0; j < OB::PER; ++j)
-      sb[j] = OB::soff(ldb, n0, wave * OB::PER + j) + uint32_t(k_lo) * OB::kstep(ldb);
-    ss = uni(ss + uint32_t(k_lo) * 2);
-    const uint32_t ka = 64 * OA::kstep(lda), kb = 64 * OB::kstep(ldb);
+      sb[j] = OB::run_part(ldb, n0, N, wave * OB::PER + j) + uint32_t(k_lo) * OB::k_part(ldb);
+    const uint32_t ss = uint32_t(k_lo) * 2;
+    const uint32_t ka = 64 * OA::k_part(lda), kb = 64 * OB::k_part(ldb);
     const uint32_t la0 = lds0 + wave * (OA::PER * 1024);
     const uint32_t lb0 = lds0 + OFF_B + wave * (OB::PER * 1024);
     auto issue = [&](int kt) {
@@ -784,8 +770,8 @@ bool wide_operands_ok(const GemmDesc& g, bool c_fp32, bool ak, bool bk) {
     return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 8 == 0;
   };
   if (!al(g.A, g.lda) || !al(g.B, g.ldb) || !al(g.C, g.ldc) || g.N % 8 != 0) return false;
-  if (!ak && g.M % 8 != 0) return false;
-  const int64_t lim = int64_t(1) << 31;  // 32-bit buffer offsets, a tile past the end included
+  if (!wide_rows_ok(ak, g.M) || !wide_rows_ok(bk, g.N)) return false;
+  const int64_t lim = int64_t(1) << 31;  // 32-bit buffer offsets
   if (((ak ? g.M : g.K) + 256) * g.lda * 2 >= lim || ((bk ? g.N : g.K) + 256) * g.ldb * 2 >= lim)
     return false;
   if (has_checks(g)) {  // the strips come from the checksums' bf16 images
