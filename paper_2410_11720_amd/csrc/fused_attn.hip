@@ -343,9 +343,10 @@ struct FusedAttn {
   using DV = Direct<false, D, NTH>;    // V image [64 keys][D dims], swizzled
   static constexpr int K_BYTES = KH * DK::BYTES;
   static constexpr int V_BYTES = 2 * DV::BYTES;
-  // tile copies through a buffer descriptor (B8 S1024 12x64: 49.8 -> 48.8 us,
-  // unprotected 31.2 -> 30.4); the protected kernel at head dim 128 measured
-  // 1-2% faster with the compiler's own copies
+  // tile copies through a buffer descriptor (B8 S1024 12x64: 46.7 -> 44.5 us
+  // and R = 32 50.6 -> 48.6, unprotected 28.9 -> 27.4; few workgroups level
+  // to 1% faster); the protected kernel at head dim 128 measured 1-2% faster
+  // with the compiler's own copies
   static constexpr bool BUF = D == 64 || !PROT;
   static constexpr int KCL = D + 8;    // K^c strip row (elements), padded
   static constexpr int KC_BYTES = PROT ? 16 * KCL * 2 : 0;
@@ -418,6 +419,17 @@ struct FusedAttn {
         qf[qb][kk] = *reinterpret_cast<const bf16x8*>(Qp + int64_t(qw + 16 * qb + lq) * ld +
                                                         32 * kk + 8 * g);
 
+    // a tile's V copies through the descriptor, apart from its other loads:
+    // they go out after the score products of the tile before, where they
+    // do not hold up the start of the tile (few workgroups: B7 S3456 3x64,
+    // R = 32, 109.9 -> 107.7 us)
+    auto issue_v = [&](int kt, int st) {
+      const uint32_t sl = lds0 + uint32_t(st) * STAGE_BYTES + K_BYTES;
+#pragma unroll
+      for (int im = 0; im < (BUF ? 2 : 0); ++im)
+        DV::issue_buf(rs, vv, ldb, uint32_t(kt * FT + 64 * im) * ldb + 2u * (2 * H + h * D),
+                      sl + im * DV::BYTES, wu);
+    };
     // checksum strip registers (loaded with a tile, written to LDS when it lands)
     float kcv[4] = {0.f, 0.f, 0.f, 0.f};
     float vrv = 0.f;
@@ -438,10 +450,6 @@ struct FusedAttn {
       for (int hf = 0; hf < (BUF ? KH : 0); ++hf)
         DK::issue_buf(rs, vk, ldb, uint32_t(key0) * ldb + 2u * (H + h * D + hf * 64),
                       sl + hf * DK::BYTES, wu);
-#pragma unroll
-      for (int im = 0; im < (BUF ? 2 : 0); ++im)
-        DV::issue_buf(rs, vv, ldb, uint32_t(key0 + 64 * im) * ldb + 2u * (2 * H + h * D),
-                      sl + K_BYTES + im * DV::BYTES, wu);
       if constexpr (PROT) {
         if (arg->check_as) {
           const int nqR = S / R;
@@ -506,14 +514,20 @@ struct FusedAttn {
     }
     float* scr = reinterpret_cast<float*>(smem + NSTAGE * STAGE_BYTES) + wave * SCR;
 
-    if (NSTAGE == 2) issue(0, 0);
+    if (NSTAGE == 2) {
+      issue(0, 0);
+      issue_v(0, 0);
+    }
     for (int kt = 0; kt < nkt; ++kt) {
       // with head dim 64 the descriptor's fields are loaded per key tile
       // (fewer scalar registers held across the loop); with 128 that costs
       // more vector registers than it saves
       arg.refresh();
       const int st = NSTAGE == 2 ? (kt & 1) : 0;
-      if (NSTAGE == 1) issue(kt, 0);
+      if (NSTAGE == 1) {
+        issue(kt, 0);
+        issue_v(kt, 0);
+      }
       wait_vmcnt<0>();
       commit(st);
       __syncthreads();  // tile kt visible; every wave is done with tile kt - 1
@@ -549,6 +563,8 @@ struct FusedAttn {
           }
         }
       }
+
+      if (NSTAGE == 2 && kt + 1 < nkt) issue_v(kt + 1, st ^ 1);
 
       // injected score faults (test-only), on the unrounded scores
       if (wf) {
@@ -1636,10 +1652,8 @@ struct FusedBwdKV : BwdTile<D> {
     }
 #pragma unroll
     for (int hf = 0; hf < (REGS ? 0 : KH); ++hf) {
-      DK::issue_buf(rs, vo, ldb, uint32_t(key0) * ldb + 2u * (H + h * D + hf * 64),
-                    lds0 + hf * DK::BYTES, wu);
-      DK::issue_buf(rs, vo, ldb, uint32_t(key0) * ldb + 2u * (2 * H + h * D + hf * 64),
-                    lds0 + OFF_V + hf * DK::BYTES, wu);
+      DK::issue(Kp, ld, key0, S, hf * 64, smem + hf * DK::BYTES, wave, lane);
+      DK::issue(Vp, ld, key0, S, hf * 64, smem + OFF_V + hf * DK::BYTES, wave, lane);
     }
     const bf16_t* zeros = reinterpret_cast<const bf16_t*>(smem + OFF_ZERO);
     if (chk && tid < T::ZERO / 4) reinterpret_cast<uint32_t*>(smem + OFF_ZERO)[tid] = 0u;
