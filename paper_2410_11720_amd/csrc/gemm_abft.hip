@@ -17,6 +17,7 @@
 // every action is appended to the device report. The tile then leaves LDS
 // in 16-byte coalesced stores.
 #include <algorithm>
+#include <type_traits>
 
 #include "abft_internal.hpp"
 #include "abft_device.hpp"
@@ -200,8 +201,14 @@ struct StripLoader {
     if (KMAJ) { r = e / BK; k = e % BK; }
     else { r = e % NR; k = e / NR; }
   }
-  // rows r0 + r exist only for r < nvalid >= 1 (the last tile may be ragged:
-  // rows past it repeat the last one); unconditional loads, as the tiles'
+  // rows r0 + r exist only for r < nvalid >= 1 (the last tile may be ragged).
+  // Unconditional loads, as the tiles': rows past the last repeat it, and
+  // store() masks them. GUARD (the one-stage tile): each load under its own
+  // bounds test, so that only the waves that hold a row issue it; there the
+  // strips are a large part of the one or two steps of K (score B8 S1024
+  // 12x64 46.7 -> 42.8 us), over long K ranges the test costs more than it
+  // saves (context B4 S1024 6x64, R = 64, 24.5 against 25.5).
+  template <bool GUARD>
   __device__ void load(const float* base, int64_t ld, int r0, int nvalid, int k0, int kend,
                        int tid) {
 #pragma unroll
@@ -209,9 +216,16 @@ struct StripLoader {
       const int e = tid + p * NT;
       int r, k;
       rk(e, r, k);
-      reg[p] = base[op_off<KMAJ>(r0 + max(min(r, nvalid - 1), 0), min(k0 + k, kend - 1), ld)];
+      if constexpr (GUARD) {
+        float v = 0.f;
+        if (r < nvalid && k0 + k < kend) v = base[op_off<KMAJ>(r0 + r, k0 + k, ld)];
+        reg[p] = v;
+      } else {
+        reg[p] = base[op_off<KMAJ>(r0 + max(min(r, nvalid - 1), 0), min(k0 + k, kend - 1), ld)];
+      }
     }
   }
+  template <bool GUARD>
   __device__ void store(T* lds, int nc, int nvalid, int k0, int kend, int tid) {
 #pragma unroll
     for (int p = 0; p < PER; ++p) {
@@ -219,7 +233,7 @@ struct StripLoader {
       int r, k;
       rk(e, r, k);
       if (r < nc) {
-        const float v = r < nvalid && k0 + k < kend ? reg[p] : 0.f;
+        const float v = GUARD || (r < nvalid && k0 + k < kend) ? reg[p] : 0.f;
         if constexpr (sizeof(T) == 2) {
           const bf16_t hi = f2bf(v);
           const bf16_t lo = f2bf(v - bf2f(hi));
@@ -451,8 +465,10 @@ struct Gemm {
   }
 
   // DIR selects the direct-to-LDS operand path (bf16 only) at compile time,
-  // so each kernel carries the registers and code of one path only.
-  template <bool DIR>
+  // so each kernel carries the registers and code of one path only; HALF its
+  // form for K ranges that end in a half stage. (One kernel for both cost the
+  // ranges of whole stages 4-10%: dV at B1 S3840 6x64 42.0 us, 37.9 now.)
+  template <bool DIR, bool HALF>
   // lin, total: the workgroup's index among this GEMM's workgroups and
   // their count (a launch of two GEMMs deals each its own range; the first
   // range is a multiple of 8 long, so both keep the dealing to the XCDs);
@@ -629,7 +645,7 @@ struct Gemm {
         auto issue_dir = [&](int kt) {
           char* st = slot(kt);
           const int kn = k_lo + kt * BK;
-          if (kn + BK <= k_hi) {
+          if (!HALF || kn + BK <= k_hi) {
             DA::issue(Ab, g.lda, m0, g.M, kn, st, wave, lane);
             DB::issue(Bb, g.ldb, n0, g.N, kn, st + DA_BYTES, wave, lane);
           } else {  // the half stage at the end of a K range (K % 64 == 32)
@@ -639,25 +655,29 @@ struct Gemm {
         };
         auto issue_strip = [&](int kt) {
           const int kn = k_lo + kt * BK;
-          if (cc && !img) ls.load(Ac, g.ldac, rc0, nc_valid, kn, k_hi, tid);
-          if (cr && !imgr) lr.load(Br, g.ldbr, qc0, nq_valid, kn, k_hi, tid);
+          if (cc && !img) ls.template load<NSTAGE == 1>(Ac, g.ldac, rc0, nc_valid, kn, k_hi, tid);
+          if (cr && !imgr) lr.template load<NSTAGE == 1>(Br, g.ldbr, qc0, nq_valid, kn, k_hi, tid);
         };
         auto commit_strip = [&](int kt) {
           T* st = reinterpret_cast<T*>(slot(kt) + DA_BYTES + DB_BYTES);
           const int kn = k_lo + kt * BK;
-          if (cc && !img) ls.store(st, nc, nc_valid, kn, k_hi, tid);
-          if (cr && !imgr) lr.store(st + r_off, nq, nq_valid, kn, k_hi, tid);
+          if (cc && !img) ls.template store<NSTAGE == 1>(st, nc, nc_valid, kn, k_hi, tid);
+          if (cr && !imgr) lr.template store<NSTAGE == 1>(st + r_off, nq, nq_valid, kn, k_hi, tid);
         };
         // the strips from their images: the column strip's rows go to
         // waves 0.., the row strip's to the waves after them; a wave copies
         // eight image rows (eight 16-byte chunks each) into the stage's strip
         // region; rows past the tile's valid ones read its last valid row
         const int wc = img ? (2 * nc + 7) / 8 : 0;
+        auto k_img = [&](int kt) {
+          const int k = k_lo + kt * BK + (lane & 7) * 8;
+          return HALF ? min(k, g.K - 8) : k;
+        };
         auto issue_img = [&](int kt) {
           if (img && wave < wc) {
             const int r = min(wave * 8 + (lane >> 3), 2 * nc_valid - 1);
             const uint16_t* src =
-                g.Aci + int64_t(2 * rc0 + r) * g.ldaci + min(k_lo + kt * BK + (lane & 7) * 8, g.K - 8);
+                g.Aci + int64_t(2 * rc0 + r) * g.ldaci + k_img(kt);
             __builtin_amdgcn_global_load_lds(
                 src, (lds_void*)(slot(kt) + DA_BYTES + DB_BYTES + wave * 1024), 16, 0, 0);
           }
@@ -665,7 +685,7 @@ struct Gemm {
             const int w = wave - wc;
             const int r = min(w * 8 + (lane >> 3), 2 * nq_valid - 1);
             const uint16_t* src =
-                g.Bri + int64_t(2 * qc0 + r) * g.ldbri + min(k_lo + kt * BK + (lane & 7) * 8, g.K - 8);
+                g.Bri + int64_t(2 * qc0 + r) * g.ldbri + k_img(kt);
             __builtin_amdgcn_global_load_lds(
                 src,
                 (lds_void*)(slot(kt) + DA_BYTES + DB_BYTES + r_off * int(sizeof(T)) + w * 1024),
@@ -677,7 +697,7 @@ struct Gemm {
           const T* sR = sS + r_off;
 #pragma unroll
           for (int kk = 0; kk < BK; kk += KI) {
-            if (kk >= kleft) break;  // (half stage: its second half is not there)
+            if (HALF && kk >= kleft) break;  // (half stage: its second half is not there)
             typename Mfma<T>::frag af[IM], bfr[JN];
             // MN-major images are read with transposing reads that are
             // waited for together
@@ -750,12 +770,12 @@ struct Gemm {
     if (nk > 0) {
       la.load(A, g.lda, m0, g.M, k_lo, k_hi, tid);
       lb.load(B, g.ldb, n0, g.N, k_lo, k_hi, tid);
-      if (cc) ls.load(Ac, g.ldac, rc0, nc_valid, k_lo, k_hi, tid);
-      if (cr) lr.load(Br, g.ldbr, qc0, nq_valid, k_lo, k_hi, tid);
+      if (cc) ls.template load<false>(Ac, g.ldac, rc0, nc_valid, k_lo, k_hi, tid);
+      if (cr) lr.template load<false>(Br, g.ldbr, qc0, nq_valid, k_lo, k_hi, tid);
       la.store(lds, k_lo, k_hi, tid);
       lb.store(lds + A_ELEMS, k_lo, k_hi, tid);
-      if (cc) ls.store(lds + A_ELEMS + B_ELEMS, nc, nc_valid, k_lo, k_hi, tid);
-      if (cr) lr.store(lds + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, k_lo, k_hi, tid);
+      if (cc) ls.template store<false>(lds + A_ELEMS + B_ELEMS, nc, nc_valid, k_lo, k_hi, tid);
+      if (cr) lr.template store<false>(lds + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, k_lo, k_hi, tid);
       __syncthreads();
     }
 
@@ -766,8 +786,8 @@ struct Gemm {
         const int kn = k_lo + (kt + 1) * BK;
         la.load(A, g.lda, m0, g.M, kn, k_hi, tid);
         lb.load(B, g.ldb, n0, g.N, kn, k_hi, tid);
-        if (cc) ls.load(Ac, g.ldac, rc0, nc_valid, kn, k_hi, tid);
-        if (cr) lr.load(Br, g.ldbr, qc0, nq_valid, kn, k_hi, tid);
+        if (cc) ls.template load<false>(Ac, g.ldac, rc0, nc_valid, kn, k_hi, tid);
+        if (cr) lr.template load<false>(Br, g.ldbr, qc0, nq_valid, kn, k_hi, tid);
       }
       const T* sA = lds + (NSTAGE >= 2 ? cur : 0) * STAGE;
       const T* sB = sA + A_ELEMS;
@@ -792,8 +812,8 @@ struct Gemm {
         const int kn = k_lo + (kt + 1) * BK;
         la.store(nA, kn, k_hi, tid);
         lb.store(nA + A_ELEMS, kn, k_hi, tid);
-        if (cc) ls.store(nA + A_ELEMS + B_ELEMS, nc, nc_valid, kn, k_hi, tid);
-        if (cr) lr.store(nA + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, kn, k_hi, tid);
+        if (cc) ls.template store<false>(nA + A_ELEMS + B_ELEMS, nc, nc_valid, kn, k_hi, tid);
+        if (cr) lr.template store<false>(nA + A_ELEMS + B_ELEMS + r_off, nq, nq_valid, kn, k_hi, tid);
       }
       __syncthreads();
     }
@@ -1549,29 +1569,33 @@ constexpr int gemm_waves_per_eu() {
   return BM * BN > 128 * 128 ? 1 : (sizeof(T) == 2 && NSTAGE == 1 && (!PROT || WLC) ? 3 : 2);
 }
 
-template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, bool DIR,
+// Operand paths: through registers, direct to LDS, direct with a half stage.
+enum Path { REGS = 0, DIRECT = 1, DIRECT_HALF = 2 };
+
+template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, Path P,
           bool WLC>
-__global__ __launch_bounds__(threads_of<T>()) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && DIR>())))
+__global__ __launch_bounds__(threads_of<T>()) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && P != REGS>())))
 void gemm_kernel(GemmDesc g) {
   extern __shared__ __align__(16) char smem[];
-  Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, WLC>::template run<DIR>(g, smem, blockIdx.x,
-                                                                      gridDim.x, 0);
+  Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, WLC>::template run<P != REGS, P == DIRECT_HALF>(
+      g, smem, blockIdx.x, gridDim.x, 0);
 }
 
 // The direct-to-LDS path needs bf16 operands, K ranges of whole 32-wide
 // half stages (K a multiple of 32; causal K ranges and split-K slices then
 // are too), 16-byte aligned operand rows, and whole 8-element chunks along the
-// M or N extent of an MN-major operand.
+// M or N extent of an MN-major operand. A one-stage tile takes whole stages
+// only (its K is a head dim).
 template <class T>
-bool direct_ok(const GemmDesc& g, bool ak, bool bk) {
-  if (sizeof(T) != 2 || g.K % 32 != 0) return false;
+Path path_of(const GemmDesc& g, bool ak, bool bk, int nstage) {
+  if (sizeof(T) != 2 || g.K % (nstage == 1 ? 64 : 32) != 0) return REGS;
   auto al = [](const void* p, int64_t ld, int64_t s0, int64_t s1) {
     return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
   };
-  if (!al(g.A, g.lda, g.sA0, g.sA1) || !al(g.B, g.ldb, g.sB0, g.sB1)) return false;
-  if (!ak && (g.M % 8 != 0 || g.M < 8)) return false;
-  if (!bk && (g.N % 8 != 0 || g.N < 8)) return false;
-  return true;
+  if (!al(g.A, g.lda, g.sA0, g.sA1) || !al(g.B, g.ldb, g.sB0, g.sB1)) return REGS;
+  if (!ak && (g.M % 8 != 0 || g.M < 8)) return REGS;
+  if (!bk && (g.N % 8 != 0 || g.N < 8)) return REGS;
+  return g.K % 64 != 0 ? DIRECT_HALF : DIRECT;
 }
 
 // Sets the dynamic-LDS limit of one kernel once (per instantiation).
@@ -1590,8 +1614,8 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   using G = Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE>;
   if (G::COLS_ONLY && (g.Br != nullptr || g.verify == 2)) return hipErrorInvalidValue;
   const bool gcc = PROT && g.Ac != nullptr, gcr = PROT && g.Br != nullptr;
-  const bool direct = direct_ok<T>(g, AK, BKM);
-  const size_t main = direct ? G::d_main_bytes(gcc, gcr) : G::main_bytes(gcc, gcr);
+  const Path path = path_of<T>(g, AK, BKM, NSTAGE);
+  const size_t main = path != REGS ? G::d_main_bytes(gcc, gcr) : G::main_bytes(gcc, gcr);
   // split-K slices skip the staged epilogue: only the operand stages (and
   // the 16 x BN checksum strip image inside them) are needed
   const size_t lds = g.splitk > 1 ? std::max(main, size_t(16 * BN * 4))
@@ -1606,37 +1630,28 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   // segments)
   if constexpr (G::MSUM)
     wlc = g.splitk <= 1 && (g.verify <= 1 || BN / 4 >= 32) && (g.Ac == nullptr || g.Rm <= BM);
-  auto kern = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, false, false>;
+  auto kern = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, REGS, false>;
   hipError_t e = hipSuccess;
-  if constexpr (sizeof(T) == 2) {
-    if (direct) {
-      if constexpr (G::MSUM) {
-        if (wlc) {
-          constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, true, true>;
-          kern = k;
-          e = set_lds_limit<k>(lds_max);
-        }
-      }
-      if (!wlc) {
-        constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, true, false>;
-        kern = k;
-        e = set_lds_limit<k>(lds_max);
-      }
-    }
-  }
-  if (!direct) {
+  auto pick = [&](auto p) {
+    constexpr Path P = decltype(p)::value;
     if constexpr (G::MSUM) {
       if (wlc) {
-        constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, false, true>;
+        constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, true>;
         kern = k;
         e = set_lds_limit<k>(lds_max);
+        return;
       }
     }
-    if (!wlc) {
-      constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, false, false>;
-      e = set_lds_limit<k>(lds_max);
-    }
+    constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, false>;
+    kern = k;
+    e = set_lds_limit<k>(lds_max);
+  };
+  if constexpr (sizeof(T) == 2) {
+    if (path == DIRECT) pick(std::integral_constant<Path, DIRECT>{});
+    if constexpr (NSTAGE > 1)
+      if (path == DIRECT_HALF) pick(std::integral_constant<Path, DIRECT_HALF>{});
   }
+  if (path == REGS) pick(std::integral_constant<Path, REGS>{});
   if (e != hipSuccess) return e;
   const int64_t ntm = (g.M + BM - 1) / BM, ntn = (g.N + BN - 1) / BN;
   const int64_t tiles = tri_tiles(g, BM, BN) ? ntm * (ntm + 1) / 2 : ntm * ntn;

@@ -164,12 +164,25 @@ def test_materialised_stages(shape):
         assert (err <= 0).all()
     dX, dW, dWo = layer.backward(dO, X, W, Wo)
     assert abft.read_report(layer.report_bwd)["n_events"] == 0
-    if dtype == "f32":
-        x2, g2 = X.view(-1, H), dO.view(-1, H)
-        dcl, dqkv = layer.tensor("dCL").view(-1, H), layer.tensor("dQKV").view(-1, 3 * H)
-        _close("QKV", layer.tensor("QKV").view(-1, 3 * H), x2, W)
-        _close("O", O.view(-1, H), layer.tensor("CL").view(-1, H), Wo)
-        _close("dCL", dcl, g2, Wo.t().contiguous())
-        _close("dWo", dWo, layer.tensor("CL").view(-1, H).t().contiguous(), g2)
-        _close("dWqkv", dW, x2.t().contiguous(), dqkv)
-        _close("dX", dX.view(-1, H), dqkv, W.t().contiguous())
+    x2, g2 = X.view(-1, H), dO.view(-1, H)
+    dcl, dqkv = layer.tensor("dCL").view(-1, H), layer.tensor("dQKV").view(-1, 3 * H)
+    _close("QKV", layer.tensor("QKV").view(-1, 3 * H), x2, W)
+    _close("O", O.view(-1, H), layer.tensor("CL").view(-1, H), Wo)
+    _close("dCL", dcl, g2, Wo.t().contiguous())
+    _close("dWo", dWo, layer.tensor("CL").view(-1, H).t().contiguous(), g2)
+    _close("dWqkv", dW, x2.t().contiguous(), dqkv)
+    _close("dX", dX.view(-1, H), dqkv, W.t().contiguous())
+    # the batched products over the keys or queries, whose K ranges end in a
+    # half stage where S % 64 = 32
+    qkv, cl, dcl, dqkv = (layer.tensor(t) for t in ("QKV", "CL", "dCL", "dQKV"))
+    for t, ap, das in zip(range(B * nh), AP.flatten(0, 1),
+                          layer.tensor("dAS").flatten(0, 1).double()):
+        b, h = t // nh, t % nh
+        das = torch.where(live, das, torch.zeros_like(das))
+        q, k, v = (qkv[b, :, i * H + h * d:i * H + (h + 1) * d] for i in range(3))
+        g, c = (x[b, :, h * d:(h + 1) * d] for x in (dcl, cl))
+        dq, dk, dv = (dqkv[b, :, i * H + h * d:i * H + (h + 1) * d] for i in range(3))
+        _close("CL", c, ap, v)
+        _close("dV", dv, ap.t().contiguous(), g)
+        _close("dQ", dq, das, k)
+        _close("dK", dk, das.t().contiguous(), q)
