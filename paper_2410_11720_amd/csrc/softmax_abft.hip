@@ -107,9 +107,12 @@ __device__ __forceinline__ void round_chunk(float (&x)[4], uint4& bits) {
 // iteration per wave; PF: prefetch the next iteration's rows; CHK: encode
 // the checksums (some of col_chk, row_chk given); NW: waves per workgroup
 // (see launch_ch). TURNS: the waves add their column sums to one LDS slab in
-// turn, and keep to the 256 registers of two waves per SIMD.
+// turn, and keep to the 256 registers of two waves per SIMD. Eight waves keep
+// to 128, for two workgroups on a CU, as the rule that picks them counts (at
+// 129 the backward of 405 workgroups took two rounds: B3 S864 5x64, R = 32,
+// 19.5 us, 14.9 now; 17.1 with four waves).
 template <class T, int CH, bool BWD, int RPI, bool PF, bool CHK, int NW, bool TURNS>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(TURNS ? 2 : 1)))
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(TURNS ? 2 : NW == 8 ? 4 : 1)))
 void softmax_kernel(SoftmaxDesc d) {
   constexpr int NT = 64 * NW;
   constexpr int V = Vec<T>::N;

@@ -1,8 +1,13 @@
-"""Wait states in the built device code. A vector memory instruction that
+"""What the built device code has to keep to.
+
+Wait states: a vector memory instruction that
 reads a scalar register needs five wait states after a vector instruction
 wrote it (v_readlane, v_readfirstlane, a compare): the compiler pads its own
 loads, but does not see the buffer copies written in assembly, whose operands
-it may have reloaded from a spill lane just before."""
+it may have reloaded from a spill lane just before.
+
+Registers: the softmax with eight waves a workgroup is chosen so that two
+workgroups share a CU, which 16 waves of at most 128 registers do."""
 import os
 import re
 import shutil
@@ -10,7 +15,9 @@ import subprocess
 
 import pytest
 
-OBJDUMP = shutil.which("llvm-objdump", path="/opt/rocm/llvm/bin:" + os.environ.get("PATH", ""))
+PATH = "/opt/rocm/llvm/bin:" + os.environ.get("PATH", "")
+OBJDUMP = shutil.which("llvm-objdump", path=PATH)
+READELF = shutil.which("llvm-readelf", path=PATH)
 WAITS = 5
 
 
@@ -62,19 +69,38 @@ def test_scan_counts_wait_states():
     assert len(short_waits(head + ["\ts_nop 3"] + load)) == 1
 
 
-@pytest.mark.skipif(OBJDUMP is None, reason="no disassembler")
-def test_buffer_copies_wait_for_their_scalars(tmp_path):
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
     from paper_2410_11720_amd import abft
-    lib = tmp_path / "lib.so"
-    shutil.copy(abft.LIB_PATH, lib)
-    subprocess.run([OBJDUMP, "--offloading", lib.name], cwd=tmp_path, check=True, capture_output=True)
-    objs = [f for f in tmp_path.iterdir() if "gfx950" in f.name and f.stat().st_size]
+    if OBJDUMP is None or READELF is None:
+        pytest.skip("no disassembler")
+    at = tmp_path_factory.mktemp("code")
+    shutil.copy(abft.LIB_PATH, at / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", "lib.so"], cwd=at, check=True, capture_output=True)
+    objs = [str(f) for f in at.iterdir() if "gfx950" in f.name and f.stat().st_size]
     assert objs
+    return objs
+
+
+def test_buffer_copies_wait_for_their_scalars(code_objects):
     copies, bad = 0, []
-    for f in objs:
-        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(f)], check=True,
+    for f in code_objects:
+        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", f], check=True,
                               capture_output=True, text=True).stdout.splitlines()
         copies += sum("buffer_load_dwordx4" in t and " lds" in t for t in text)
         bad += short_waits(text)
     assert copies > 0
     assert not bad, f"{len(bad)} short of {WAITS} wait states, first: {bad[:4]}"
+
+
+def test_eight_wave_softmax_fits_twice(code_objects):
+    seen = {}
+    for f in code_objects:
+        text = subprocess.run([READELF, "--notes", f], check=True, capture_output=True,
+                              text=True).stdout
+        for k in re.split(r"\n\s+- \.agpr_count:", text)[1:]:
+            name = re.search(r"\.name:\s+(\S+)", k).group(1)
+            if re.search(r"softmax_kernelI.*Li8ELb0EEEv", name):
+                seen[name] = int(re.search(r"\.vgpr_count:\s+(\d+)", k).group(1))
+    assert len(seen) == 16  # two types, one or two chunks, both directions, checked or not
+    assert max(seen.values()) <= 128, {k: v for k, v in seen.items() if v > 128}
