@@ -13,6 +13,8 @@
 // layout; a flagged one is corrected with one thread per vector (the
 // paper's Fig. 4 mapping), from the checksums only (DELTA or RECONSTRUCT),
 // since no operands are at hand.
+#include <algorithm>
+
 #include "abft_internal.hpp"
 #include "abft_device.hpp"
 
@@ -356,20 +358,21 @@ __device__ __forceinline__ bool slab_flagged(const T* M, int64_t ld, int64_t c_l
   return __syncthreads_or(flag);
 }
 
-// CPS: chunks of the fast detection (0: one thread per vector)
+// CPS: chunks of the fast detection (0: one thread per vector). Slabs of
+// `slab` columns; nrb row blocks in a row, bps of them in a slab (the launch
+// divides: 64-bit divisions here were 0.4 us of a small matrix's 26).
 template <class T, int CPS>
 __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t cols, int64_t ld,
-                                                    int64_t bstride, int Rb, int Cb, int slab,
+                                                    int64_t bstride, int Rb, int Cb, int64_t slab,
+                                                    int64_t nrb, int bps,
                                                     float* col_chk, float* row_chk, float tn,
                                                     float tc, float e_rel, int op_tag,
                                                     abft_report* rep) {
   extern __shared__ __align__(16) char smem[];
-  const int64_t nslab = (cols + slab - 1) / slab;
-  const int64_t sl = blockIdx.x % nslab, rb = blockIdx.x / nslab, b = blockIdx.y;
+  const int64_t rb = blockIdx.x, b = blockIdx.y, sl = blockIdx.z;
   const int64_t c_lo = sl * slab, c_hi = c_lo + slab < cols ? c_lo + slab : cols;
-  const int64_t nrb = row_chk ? cols / Cb : 0;          // row blocks of a row
-  const int64_t b_lo = row_chk ? c_lo / Cb : 0;         // the slab's first
-  const int64_t nsb = row_chk ? (c_hi - c_lo) / Cb : 0; // and how many
+  const int64_t b_lo = sl * bps;  // the slab's first row block, and how many
+  const int nsb = int(b_lo + bps < nrb ? bps : nrb - b_lo);
   int* rowcnt = reinterpret_cast<int*>(smem);           // [Rb][nsb]
   int* colcnt = rowcnt + Rb * nsb;                      // [c_hi - c_lo]
   T* M = C + b * bstride + rb * Rb * ld;
@@ -377,8 +380,8 @@ __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t 
   float* rc = row_chk ? row_chk + (b * rows + rb * Rb) * nrb * 2 : nullptr;
   const int tid = threadIdx.x;
   // row vector u of the slab: row u / nsb, row block b_lo + u % nsb
-  auto rvec = [&](int64_t u) { return M + (u / nsb) * ld + (b_lo + u % nsb) * Cb; };
-  auto rchk = [&](int64_t u) { return rc + ((u / nsb) * nrb + b_lo + u % nsb) * 2; };
+  auto rvec = [&](int u) { return M + (u / nsb) * ld + (b_lo + u % nsb) * Cb; };
+  auto rchk = [&](int u) { return rc + ((u / nsb) * nrb + b_lo + u % nsb) * 2; };
 
   // quick clean check: any flagged vector?
   if constexpr (CPS > 0) {
@@ -386,10 +389,12 @@ __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t 
                                               e_rel))
       return;
   } else {
+    // the row vectors start at the waves the columns left over: a narrow slab
+    // is one vector's latency, not two
     bool my = false;
     for (int64_t n = c_lo + tid; n < c_hi; n += NT)
       my |= vec_flagged<T>(M + n, int(ld), Rb, cc[n], e_rel);
-    for (int64_t u = tid; u < Rb * nsb; u += NT)
+    for (int u = (tid - int(c_hi - c_lo)) & (NT - 1); u < Rb * nsb; u += NT)
       my |= vec_flagged<T>(rvec(u), 1, Cb, rchk(u)[0], e_rel);
     if (!__syncthreads_or(my)) return;
   }
@@ -409,17 +414,17 @@ __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t 
     const EecResult r = eec_locate<T>(vec, int(ld), Rb, cc[n], cc[cols + n], e_rel, tn);
     if (r.status == EEC_LOCATED) {
       fix(vec, int(ld), Rb, r.index, cc[n], r.d1, int(rb * Rb + r.index), int(n));
-      if (row_chk) atomicAdd(&rowcnt[r.index * nsb + (n - c_lo) / Cb], 1);
+      if (row_chk) atomicAdd(&rowcnt[r.index * nsb + int(n - c_lo) / Cb], 1);
     }
   }
   wg_sync_global();
   if (row_chk) {
     // 2a. refresh row checksums of 1R-corrected row vectors
-    for (int64_t u = tid; u < Rb * nsb; u += NT)
+    for (int u = tid; u < Rb * nsb; u += NT)
       if (rowcnt[u] >= 2) vec_checksums<T>(rvec(u), 1, Cb, rchk(u), rchk(u) + 1);
     wg_sync_global();
     // 2b. row pass
-    for (int64_t u = tid; u < Rb * nsb; u += NT) {
+    for (int u = tid; u < Rb * nsb; u += NT) {
       T* vec = rvec(u);
       const float* k = rchk(u);
       const EecResult r = eec_locate<T>(vec, 1, Cb, k[0], k[1], e_rel, tn);
@@ -440,7 +445,7 @@ __global__ __launch_bounds__(NT) void verify_kernel(T* C, int64_t rows, int64_t 
     if (vec_flagged<T>(M + n, int(ld), Rb, cc[n], e_rel))
       record_event(rep, op_tag, int(b), 0, int(rb * Rb), int(n), ABFT_KIND_NONE,
                    ABFT_ACT_UNCORRECTABLE, 0.f);
-  for (int64_t u = tid; u < Rb * nsb; u += NT)
+  for (int u = tid; u < Rb * nsb; u += NT)
     if (vec_flagged<T>(rvec(u), 1, Cb, rchk(u)[0], e_rel))
       record_event(rep, op_tag, int(b), 0, int(rb * Rb + u / nsb), int((b_lo + u % nsb) * Cb),
                    ABFT_KIND_NONE, ABFT_ACT_UNCORRECTABLE, 0.f);
@@ -602,18 +607,22 @@ hipError_t verify_t(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(unsigned((cols + slab - 1) / slab * (rows / Rb)), unsigned(batch));
-  hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, C, rows, cols, ld, bs, Rb, Cb, int(slab), col_chk,
-                     row_chk, tn, tc, e_rel, op_tag, report);
+  const int64_t nslab = (cols + slab - 1) / slab, nrb = row_chk ? cols / Cb : 0;
+  const dim3 grid(unsigned(rows / Rb), unsigned(batch), unsigned(nslab));
+  hipLaunchKernelGGL(k, grid, dim3(NT), lds, s, C, rows, cols, ld, bs, Rb, Cb, slab, nrb,
+                     row_chk ? int(slab / Cb) : 0, col_chk, row_chk, tn, tc, e_rel, op_tag, report);
   return hipGetLastError();
 }
 
 // The chunked detection takes what the encoder's vector path takes (aligned
 // rows, row blocks of a power of two of at most 16 chunks); slabs of 8
-// chunks, 16 where a row block needs them. Any other shape: one thread per
-// vector over slabs of about 256 columns. Where the correction's counters
-// would not fit beside the detection's LDS, or the slabs of a launch not its
-// grid, a workgroup takes whole rows.
+// chunks, 16 where a row block needs them (32 would be slower: the sums over
+// 32 lanes, 8 x 128 x 128 fp32 24.1 us against 21.5). Any other shape, and one
+// whose correction's counters would not fit beside the detection's LDS: one
+// thread per vector, over slabs of about 256 columns while the row blocks
+// alone do not fill the chip (8 x 1024 x 768 fp32, 64 row blocks, 58 -> 38 us
+// as slabs; 8 x 700 x 900 in blocks of 7, 800 of them, 73 -> 77). Where the
+// slabs do not fit the grid, a workgroup takes whole rows.
 template <class T>
 hipError_t verify_d(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t bs, int Rb,
                     int Cb, float* col_chk, float* row_chk, float tn, float tc, float e_rel,
@@ -626,12 +635,14 @@ hipError_t verify_d(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld,
     fast = fast && Cb % V == 0 && l >= 1 && (l & (l - 1)) == 0 && l <= 16;
     cps = l > 8 ? 16 : 8;
   }
-  int64_t slab = fast ? cps * V : (row_chk != nullptr ? (255 / Cb + 1) * int64_t(Cb) : 256);
-  slab = slab < cols ? slab : cols;
+  int64_t slab = std::min<int64_t>(cps * V, cols);
   const int64_t counters = row_chk != nullptr ? Rb * (slab / Cb) + slab : 0;
   fast = fast && counters <= 128 * 1024 / 4;
-  if (!fast && counters > 150 * 1024 / 4) slab = cols;
-  if ((cols + slab - 1) / slab * (rows / Rb) > (int64_t(1) << 24) - 1) {
+  if (!fast) {
+    slab = row_chk != nullptr ? (255 / Cb + 1) * int64_t(Cb) : 256;
+    if (slab > cols || rows / Rb * batch >= 512) slab = cols;
+  }
+  if ((cols + slab - 1) / slab > 0xffff) {
     fast = false;
     slab = cols;
   }

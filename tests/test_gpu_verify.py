@@ -14,11 +14,14 @@ pytestmark = pytest.mark.gpu
 
 # dtype, rows, cols, ld, block rows, block cols (0: columns only): slabs of 8
 # and of 16 chunks, a ragged last slab, a matrix narrower than a slab, an
-# unaligned leading dimension, a row block no lane group covers
+# unaligned leading dimension, a row block no lane group covers, whole rows
+# where the row blocks fill the chip
 CASES = [("bf16", 256, 320, 320, 128, 64), ("bf16", 128, 384, 384, 32, 128),
          ("bf16", 96, 200, 208, 32, 8), ("bf16", 64, 8, 8, 64, 8), ("bf16", 256, 200, 208, 128, 0),
          ("bf16", 128, 192, 193, 64, 64), ("bf16", 128, 576, 576, 64, 192),
-         ("f32", 128, 160, 160, 64, 32), ("f32", 192, 128, 128, 64, 64), ("f32", 70, 90, 91, 7, 9)]
+         ("f32", 128, 160, 160, 64, 32), ("f32", 192, 128, 128, 64, 64), ("f32", 70, 90, 91, 7, 9),
+         ("f32", 256, 384, 384, 128, 128), ("bf16", 96, 768, 768, 32, 256),
+         ("bf16", 1204, 270, 271, 7, 9)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
