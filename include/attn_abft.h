@@ -142,7 +142,11 @@ typedef struct {
   float   t_near_inf;                /* Sec. 4.2, default 1e10 (compared as stored) */
   float   t_correct;                 /* Sec. 4.2, default 1e5                   */
   float   e_rel;                     /* detection bound E = e_rel * sum|v|; 0 ->
-                                        2^-4 (bf16) / 2^-13 (fp32)              */
+                                        2^-4 (bf16) / 2^-13 (fp32). Outputs
+                                        stored in bf16 carry its rounding, and
+                                        the fused backward at head_dim 64 sums
+                                        its scores rounded to bf16: an e_rel
+                                        near 2^-9 flags clean vectors           */
   uint32_t sections;                 /* ABFT_SEC_* enabled this call; a forward
                                         whose backward is protected must have
                                         ABFT_SEC_BWD set (it saves the checksums

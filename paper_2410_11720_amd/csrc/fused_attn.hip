@@ -1038,17 +1038,18 @@ struct BwdTile {
   // entities cbase + 0..15, rows rbase + 0..127 (see score_locate for A, Bm
   // and tr). A flagged vector is gathered into the wave's scratch and fixed
   // by lane 0; the fixed element is put back into the tile.
-  template <bool TR, bool MSUM>
+  template <bool TR>
   __device__ static void check(floatx4 (&t)[8], const floatx4& cs, const FusedBwdDesc& fd, int op,
                                int b, int h, int cbase, int rbase, const bf16_t* A,
                                const bf16_t* Bm, int64_t lda, int64_t ldb, float* scr, int lane) {
     const int lq = lane & 15, g = lane >> 4;
     const int R = fd.R, NB = FT / R, lg_jpb = __builtin_ctz(R / 16);
     float mine1 = 0.f, minea = 0.f;
-    if constexpr (MSUM) {
+    if constexpr (D == 64) {
       // Each column's sums over the rows of every R-row block on the matrix
       // cores: the values and their magnitudes packed to bf16 (a rounding of
-      // 2^-9 relative, far inside the detection bound E) as the B operand,
+      // 2^-9 relative, far inside the detection bound E unless the caller
+      // asks for an e_rel near it or below) as the B operand,
       // one slab of 32 rows per MFMA, against a block-indicator A operand
       // whose row 4 b is block b's: row 4 b of the result, register 0 of
       // lane group b, is block b's sum.
@@ -1069,32 +1070,25 @@ struct BwdTile {
       mine1 = vs[0];
       minea = as[0];
     } else {
-      // the same sums on the vector ALUs (the key pass at head dim 128: the
-      // matrix-core form holds registers it does not have)
-      float sj[8], aj[8];
+      // The same sums in fp32: over eight rows on the vector ALUs, over the
+      // lane groups (k = the group) and the rest of a block by an fp32 MFMA
+      // against the same indicator, in straight-line code whatever R is. B4
+      // S2048 32x128, query pass 386 us (lane exchanges instead of the MFMAs
+      // 433; the sums above, of values rounded to bf16, 355), key pass 737
+      // (766; 758).
+      floatx4 vs = {0.f, 0.f, 0.f, 0.f}, as = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        sj[j] = (t[j][0] + t[j][1]) + (t[j][2] + t[j][3]);
-        aj[j] = (fabsf(t[j][0]) + fabsf(t[j][1])) + (fabsf(t[j][2]) + fabsf(t[j][3]));
+      for (int q = 0; q < 4; ++q) {
+        const floatx4 &x = t[2 * q], &y = t[2 * q + 1];
+        const float sv = ((x[0] + x[1]) + (x[2] + x[3])) + ((y[0] + y[1]) + (y[2] + y[3]));
+        const float sm = ((fabsf(x[0]) + fabsf(x[1])) + (fabsf(x[2]) + fabsf(x[3]))) +
+                         ((fabsf(y[0]) + fabsf(y[1])) + (fabsf(y[2]) + fabsf(y[3])));
+        const float one = lq == 4 * ((32 * q) >> (lg_jpb + 4)) ? 1.f : 0.f;
+        vs = __builtin_amdgcn_mfma_f32_16x16x4f32(one, sv, vs, 0, 0, 0);
+        as = __builtin_amdgcn_mfma_f32_16x16x4f32(one, sm, as, 0, 0, 0);
       }
-      float r1[4], ra[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        r1[i] = sj[2 * i] + sj[2 * i + 1];
-        ra[i] = aj[2 * i] + aj[2 * i + 1];
-      }
-      if (lg_jpb >= 2) {
-        r1[0] += r1[1]; ra[0] += ra[1];
-        r1[1] = r1[2] + r1[3]; ra[1] = ra[2] + ra[3];
-      }
-      if (lg_jpb >= 3) { r1[0] += r1[1]; ra[0] += ra[1]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if (i < NB) {
-          const float t1 = group4_sum(r1[i]), ta = group4_sum(ra[i]);
-          if (g == i) { mine1 = t1; minea = ta; }
-        }
-      }
+      mine1 = vs[0];
+      minea = as[0];
     }
     const float c1 = cs[0] + cs[1];
     uint64_t mask = __ballot(g < NB && flagged(c1 - mine1, minea, fd.e_rel));
@@ -1319,8 +1313,8 @@ struct BwdTile {
 // dim 128 the two stages leave no room for those: each wave holds its 16
 // queries' fragments in 32 registers. (One stage, the images in LDS: every
 // tile waited for its loads, 9 us a tile even on an idle GPU; B4 S2048 H4096
-// 32x128 614 -> 537 us, and with head dim 64's elementwise code and checks on
-// the matrix cores, which the registers then allowed, 373.)
+// 32x128 614 -> 537 us, and with head dim 64's elementwise code and check sums on
+// the matrix cores, which the registers then allowed, 386.)
 template <int D, bool CHK>
 struct FusedBwdQ : BwdTile<D> {
   using T = BwdTile<D>;
@@ -1490,7 +1484,7 @@ struct FusedBwdQ : BwdTile<D> {
         }
         if (wf) T::template inject<false>(s, fd, ABFT_OP_AS, b, h, qw, key0, lane);
         if (chk)
-          T::template check<false, true>(s, ks, fd, ABFT_OP_AS, b, h, qw, key0, Qp, Kp, ld, ld, scr, lane);
+          T::template check<false>(s, ks, fd, ABFT_OP_AS, b, h, qw, key0, Qp, Kp, ld, ld, scr, lane);
         // masked keys (diagonal tile only) enter the exponential as -inf
         auto probs = [&](auto masked) {
 #pragma unroll
@@ -1530,7 +1524,7 @@ struct FusedBwdQ : BwdTile<D> {
         }
         if (wf) T::template inject<false>(dp, fd, ABFT_OP_DAP, b, h, qw, key0, lane);
         if (chk)
-          T::template check<false, true>(dp, vs, fd, ABFT_OP_DAP, b, h, qw, key0, dCLp, Vp, H, ld, scr,
+          T::template check<false>(dp, vs, fd, ABFT_OP_DAP, b, h, qw, key0, dCLp, Vp, H, ld, scr,
                                    lane);
         auto grads = [&](auto masked) {
 #pragma unroll
@@ -1582,7 +1576,7 @@ struct FusedBwdQ : BwdTile<D> {
 // scratch. Bound by vector ALU work; at head dim 128 P and dS took about 16
 // instructions an element in a masked, twice rounded form, now four (the mask
 // in a copy of its own): B4 S2048 H4096 32x128 1090 -> 850 us, with PART 1's
-// two stages and matrix-core checks 760; unprotected 627 -> 517.
+// two stages and the check sums on the matrix cores 737; unprotected 627 -> 517.
 // PART 0 forms dV and dK together; where both sets of accumulators do not
 // fit the registers of two waves per SIMD (head dim 128) the pass runs as
 // PART 1 (S, P, dV) then PART 2 (S, P, dP, dS, dK), each recomputing and
@@ -1779,7 +1773,7 @@ struct FusedBwdKV : BwdTile<D> {
         }
         if (DO_K && wf) T::template inject<true>(s, fd, ABFT_OP_AS, b, h, kw, q0, lane);
         if (chk)
-          T::template check<true, D == 64 || PART == 1>(s, cs, fd, ABFT_OP_AS, b, h, kw, q0, Kp, Qp, ld, ld, scr, lane);
+          T::template check<true>(s, cs, fd, ABFT_OP_AS, b, h, kw, q0, Kp, Qp, ld, ld, scr, lane);
         // masked queries (diagonal tile only) enter the exponential as -inf
         auto probs = [&](auto masked) {
 #pragma unroll
@@ -1835,7 +1829,7 @@ struct FusedBwdKV : BwdTile<D> {
         }
         if (wf) T::template inject<true>(dp, fd, ABFT_OP_DAP, b, h, kw, q0, lane);
         if (chk)
-          T::template check<true, D == 64 || PART == 1>(dp, cs, fd, ABFT_OP_DAP, b, h, kw, q0, Vp, dCLp, ld, H, scr,
+          T::template check<true>(dp, cs, fd, ABFT_OP_DAP, b, h, kw, q0, Vp, dCLp, ld, H, scr,
                                   lane);
         auto grads = [&](auto masked) {
 #pragma unroll
