@@ -278,7 +278,8 @@ def run_fused_training(shape, faults=(), seed=1):
 
 
 @pytest.mark.parametrize("causal", [False, True])
-@pytest.mark.parametrize("R,H", [(128, 128), (64, 128), (128, 256)], ids=["d64r128", "d64r64", "d128"])
+@pytest.mark.parametrize("R,H", [(128, 128), (64, 128), (128, 256), (64, 256), (32, 256)],
+                         ids=["d64r128", "d64r64", "d128", "d128r64", "d128r32"])
 def test_fused_forward_backward(causal, R, H):
     shape = W.make_shape(2, 256, H, 2, causal=causal, block_rows=R, name="train")
     g, o, ob = run_fused_training(shape)
@@ -327,7 +328,8 @@ def check_training_outputs(g, o, ob, shape):
         assert nrel <= RTOL, f"{k} vs materialised: relative norm {nrel:.3g}"
 
 
-@pytest.mark.parametrize("R,H", [(128, 128), (64, 128), (128, 256)], ids=["d64r128", "d64r64", "d128"])
+@pytest.mark.parametrize("R,H", [(128, 128), (64, 128), (128, 256), (64, 256), (32, 256)],
+                         ids=["d64r128", "d64r64", "d128", "d128r64", "d128r32"])
 def test_fused_backward_faults(R, H):
     """Faults in the scores (the forward's and both backward passes'
     recomputations see them), dP, dV, dK, dQ and dX: each located where
