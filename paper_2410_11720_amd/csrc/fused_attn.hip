@@ -397,9 +397,10 @@ struct FusedAttn {
     const bf16_t* base = static_cast<const bf16_t*>(arg->qkv) + int64_t(b) * S * ld;
     const bf16_t* Qp = base + h * D;
     const bf16_t* Kp = base + H + h * D;
-    // this batch element's rows as a copy source (3 H columns: Q | K | V)
+    // a tile's rows as a copy source (3 H columns: Q | K | V); the offsets
+    // within it are 32 bits for any S and H
     const uint32_t ldb = 6u * uint32_t(H);
-    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
+    auto rows_at = [&](int row) { return rsrc_of(base + row * ld, uint32_t(FT) * ldb); };
     const uint32_t vk = DK::voff(ldb, lane), vv = DV::voff(ldb, lane);
     const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int nkt = arg->causal ? qt + 1 : nqt;
@@ -425,9 +426,10 @@ struct FusedAttn {
     // R = 32, 109.9 -> 107.7 us)
     auto issue_v = [&](int kt, int st) {
       const uint32_t sl = lds0 + uint32_t(st) * STAGE_BYTES + K_BYTES;
+      const u32x4 rs = rows_at(kt * FT);
 #pragma unroll
       for (int im = 0; im < (BUF ? 2 : 0); ++im)
-        DV::issue_buf(rs, vv, ldb, uint32_t(kt * FT + 64 * im) * ldb + 2u * (2 * H + h * D),
+        DV::issue_buf(rs, vv, ldb, uint32_t(64 * im) * ldb + 2u * (2 * H + h * D),
                       sl + im * DV::BYTES, wu);
     };
     // checksum strip registers (loaded with a tile, written to LDS when it lands)
@@ -446,10 +448,10 @@ struct FusedAttn {
         for (int im = 0; im < 2; ++im)
           DV::issue(Vp, ld, 0, D, key0 + 64 * im, sb + K_BYTES + im * DV::BYTES, wave, lane);
       }
+      const u32x4 rs = rows_at(key0);
 #pragma unroll
       for (int hf = 0; hf < (BUF ? KH : 0); ++hf)
-        DK::issue_buf(rs, vk, ldb, uint32_t(key0) * ldb + 2u * (H + h * D + hf * 64),
-                      sl + hf * DK::BYTES, wu);
+        DK::issue_buf(rs, vk, ldb, 2u * (H + h * D + hf * 64), sl + hf * DK::BYTES, wu);
       if constexpr (PROT) {
         if (arg->check_as) {
           const int nqR = S / R;
@@ -1348,9 +1350,10 @@ struct FusedBwdQ : BwdTile<D> {
     const bf16_t* Vp = base + 2 * H + h * D;
     const bf16_t* dCLp = static_cast<const bf16_t*>(fd.dcl) + int64_t(b) * S * H + h * D;
     const bf16_t* CLp = static_cast<const bf16_t*>(fd.cl) + int64_t(b) * S * H + h * D;
-    // this batch element's rows as copy sources
+    // a tile's rows as copy sources; the offsets within it are 32 bits for
+    // any S and H
     const uint32_t ldb = 6u * uint32_t(H), ldg = 2u * uint32_t(H);
-    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
+    auto rows_at = [&](int row) { return rsrc_of(base + row * ld, uint32_t(FT) * ldb); };
     const uint32_t vo = DK::voff(ldb, lane);
     const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int nkt = fd.causal ? qt + 1 : nqt;
@@ -1391,14 +1394,13 @@ struct FusedBwdQ : BwdTile<D> {
       }
     }
     if constexpr (!REGS) {
-      const u32x4 rg = rsrc_of(dCLp - h * D, uint32_t(S) * ldg);
+      const u32x4 rs = rows_at(q0);
+      const u32x4 rg = rsrc_of(dCLp - h * D + int64_t(q0) * H, uint32_t(FT) * ldg);
       const uint32_t vg = DK::voff(ldg, lane);
 #pragma unroll
       for (int hf = 0; hf < KH; ++hf) {
-        DK::issue_buf(rs, vo, ldb, uint32_t(q0) * ldb + 2u * (h * D + hf * 64),
-                      lds0 + OFF_Q + hf * DK::BYTES, wu);
-        DK::issue_buf(rg, vg, ldg, uint32_t(q0) * ldg + 2u * (h * D + hf * 64),
-                      lds0 + OFF_G + hf * DK::BYTES, wu);
+        DK::issue_buf(rs, vo, ldb, 2u * (h * D + hf * 64), lds0 + OFF_Q + hf * DK::BYTES, wu);
+        DK::issue_buf(rg, vg, ldg, 2u * (h * D + hf * 64), lds0 + OFF_G + hf * DK::BYTES, wu);
       }
     }
     const bf16_t* zeros = reinterpret_cast<const bf16_t*>(smem + OFF_ZERO);
@@ -1418,12 +1420,12 @@ struct FusedBwdQ : BwdTile<D> {
       }
     };
     auto issue_copies = [&](int kt, int st) {
-      const uint32_t sl = lds0 + uint32_t(st) * STAGE, row = uint32_t(kt * FT) * ldb;
+      const uint32_t sl = lds0 + uint32_t(st) * STAGE;
+      const u32x4 rs = rows_at(kt * FT);
 #pragma unroll
       for (int hf = 0; hf < KH; ++hf) {
-        DK::issue_buf(rs, vo, ldb, row + 2u * (H + h * D + hf * 64), sl + hf * DK::BYTES, wu);
-        DK::issue_buf(rs, vo, ldb, row + 2u * (2 * H + h * D + hf * 64),
-                      sl + OFF_V + hf * DK::BYTES, wu);
+        DK::issue_buf(rs, vo, ldb, 2u * (H + h * D + hf * 64), sl + hf * DK::BYTES, wu);
+        DK::issue_buf(rs, vo, ldb, 2u * (2 * H + h * D + hf * 64), sl + OFF_V + hf * DK::BYTES, wu);
       }
     };
     auto commit = [&](int st) {
@@ -1621,10 +1623,9 @@ struct FusedBwdKV : BwdTile<D> {
     const bf16_t* Kp = base + H + h * D;
     const bf16_t* Vp = base + 2 * H + h * D;
     const bf16_t* dCLp = static_cast<const bf16_t*>(fd.dcl) + int64_t(b) * S * H + h * D;
-    // this batch element's rows as copy sources
+    // (copies through descriptors: of a tile's rows, so that the offsets are
+    // 32 bits for any S and H)
     const uint32_t ldb = 6u * uint32_t(H), ldg = 2u * uint32_t(H);
-    const u32x4 rs = rsrc_of(base, uint32_t(S) * ldb);
-    const u32x4 rg = rsrc_of(dCLp - h * D, uint32_t(S) * ldg);
     const uint32_t vo = DK::voff(ldb, lane), vg = DK::voff(ldg, lane);
     const uint32_t lds0 = lds_addr(smem), wu = uni(wave);
     const int qt0 = fd.causal ? kt : 0;
@@ -1685,13 +1686,15 @@ struct FusedBwdKV : BwdTile<D> {
           DK::issue(dCLp, H, qt * FT, S, hf * 64, sb + OFF_G + hf * DK::BYTES, wave, lane);
         }
       }
-      const uint32_t sl = lds0 + OFF_ST + uint32_t(st) * STAGE, q0 = uint32_t(qt * FT);
+      if constexpr (BUF) {
+        const uint32_t sl = lds0 + OFF_ST + uint32_t(st) * STAGE;
+        const u32x4 rs = rsrc_of(base + int64_t(qt * FT) * ld, uint32_t(FT) * ldb);
+        const u32x4 rg = rsrc_of(dCLp - h * D + int64_t(qt * FT) * H, uint32_t(FT) * ldg);
 #pragma unroll
-      for (int hf = 0; hf < (BUF ? KH : 0); ++hf) {
-        DK::issue_buf(rs, vo, ldb, q0 * ldb + 2u * (h * D + hf * 64), sl + OFF_Q + hf * DK::BYTES,
-                      wu);
-        DK::issue_buf(rg, vg, ldg, q0 * ldg + 2u * (h * D + hf * 64), sl + OFF_G + hf * DK::BYTES,
-                      wu);
+        for (int hf = 0; hf < KH; ++hf) {
+          DK::issue_buf(rs, vo, ldb, 2u * (h * D + hf * 64), sl + OFF_Q + hf * DK::BYTES, wu);
+          DK::issue_buf(rg, vg, ldg, 2u * (h * D + hf * 64), sl + OFF_G + hf * DK::BYTES, wu);
+        }
       }
     };
     auto commit = [&](int st) {

@@ -326,3 +326,40 @@ def test_c5_fault_sweep(c5, count, mag):
 def test_c5_stages_sampled_heads(c5):
     lay, _ = c5
     check_stages(lay, 39, 0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fused_core_rows_past_four_gigabytes(d):
+    """A layer so wide that the byte offsets of one sequence's Q | K | V rows
+    leave 32 bits (S * 6 H = 4.8e9): the fused forward and backward core on
+    random Q, K, V and dCL, sampled heads against fp64 products of them
+    (1e-2 in relative norm: P, dS and the outputs in bf16)."""
+    from paper_2410_11720_amd import abft
+    S, H = 4096, 196608
+    cfg = abft.LayerConfig(1, S, H, H // d, causal=True, fused=True, protect=False)
+    layer = abft.ProtectedAttention(cfg, capacity=16)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    QKV, dCL, CL, dQKV = (layer.tensor(t)[0] for t in ("QKV", "dCL", "CL", "dQKV"))
+    for t in (QKV, dCL):
+        for r in range(0, S, 512):
+            t[r:r + 512] = torch.randn(512, t.shape[1], generator=gen, device="cuda").bfloat16()
+    dummy = torch.zeros(16, dtype=torch.bfloat16, device="cuda")
+    grad = torch.zeros(16, dtype=torch.float32, device="cuda")
+    abft.attn_abft_forward_stages(cfg, dummy, dummy, dummy, dummy, layer.workspace, None, 0,
+                                  layer.report, abft.FWD_STAGES["score"])
+    abft.attn_abft_backward_stages(cfg, dummy, dummy, dummy, dummy, layer.workspace, dummy, grad,
+                                   grad, None, 0, layer.report_bwd, 0x400)
+    mask = torch.ones(S, S, dtype=torch.bool, device="cuda").triu(1)
+    for h in (0, H // d // 2 + 1, H // d - 1):
+        q, k, v = (QKV[:, i * H + h * d:i * H + (h + 1) * d].double() for i in range(3))
+        g = dCL[:, h * d:(h + 1) * d].double()
+        P = torch.softmax((q @ k.t().contiguous() / d ** 0.5).masked_fill(mask, float("-inf")), -1)
+        c = P @ v
+        dS = P * (g @ v.t().contiguous() - (c * g).sum(1, keepdim=True)) / d ** 0.5
+        ref = dict(CL=c, dQ=dS @ k, dK=dS.t().contiguous() @ q, dV=P.t().contiguous() @ g)
+        got = dict(CL=CL[:, h * d:(h + 1) * d])
+        got.update((n, dQKV[:, i * H + h * d:i * H + (h + 1) * d]) for i, n in enumerate(("dQ", "dK", "dV")))
+        for n in ref:
+            for rows in (slice(0, S), slice(S - 128, S)):
+                e, r = (got[n][rows].double() - ref[n][rows]).norm(), ref[n][rows].norm()
+                assert (e / r).item() <= 1e-2, (n, h, rows)
