@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "attn_abft.h"
 
 namespace abft {
@@ -241,6 +243,23 @@ struct EncodeJob {
 };
 hipError_t launch_encode_jobs(const EncodeJob* jobs, int n, int dtype, abft_report* reset,
                               hipStream_t stream);
+
+// Sets the dynamic-LDS limit of one kernel, once per device (the attribute
+// belongs to the current device's copy of the kernel); safe from several
+// threads.
+template <auto KERN>
+hipError_t lds_limit(size_t bytes) {
+  static std::atomic<uint64_t> done{0};
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const uint64_t bit = uint64_t(1) << (dev & 63);
+  if (dev < 64 && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
+  if (e == hipSuccess && dev < 64) done.fetch_or(bit, std::memory_order_release);
+  return e;
+}
 
 // Threshold as the storage dtype represents it (round to nearest even).
 float stored_threshold(float t, int dtype);

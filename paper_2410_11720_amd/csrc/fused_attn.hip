@@ -1908,14 +1908,8 @@ void fused_attn_kernel(FusedDesc fd) {
 template <int D, bool PROT>
 hipError_t launch_d(const FusedDesc& fd, hipStream_t s) {
   using F = FusedAttn<D, PROT>;
-  static bool attr = false;
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fused_attn_kernel<D, PROT>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             F::LDS_BYTES);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  const hipError_t e = lds_limit<fused_attn_kernel<D, PROT>>(F::LDS_BYTES);
+  if (e != hipSuccess) return e;
   const int64_t grid = int64_t(fd.B) * fd.nh * (fd.S / FT);
   if (grid == 0) return hipSuccess;
   auto kern = fused_attn_kernel<D, PROT>;
@@ -1925,13 +1919,8 @@ hipError_t launch_d(const FusedDesc& fd, hipStream_t s) {
 
 template <auto KERN>
 hipError_t launch_bwd_kernel(const FusedBwdDesc& fd, int lds, hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-    attr = true;
-  }
+  const hipError_t e = lds_limit<KERN>(lds);
+  if (e != hipSuccess) return e;
   const int64_t grid = int64_t(fd.B) * fd.nh * (fd.S / FT);
   if (grid == 0) return hipSuccess;
   hipLaunchKernelGGL(KERN, dim3(unsigned(grid)), dim3(BNT), lds, s, fd);

@@ -1598,17 +1598,6 @@ Path path_of(const GemmDesc& g, bool ak, bool bk, int nstage) {
   return g.K % 64 != 0 ? DIRECT_HALF : DIRECT;
 }
 
-// Sets the dynamic-LDS limit of one kernel once (per instantiation).
-template <auto KERN>
-hipError_t set_lds_limit(size_t bytes) {
-  static bool done = false;  // harmless if repeated
-  if (done) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(KERN),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-  if (e == hipSuccess) done = true;
-  return e;
-}
-
 template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE = 2>
 hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   using G = Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE>;
@@ -1638,13 +1627,13 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
       if (wlc) {
         constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, true>;
         kern = k;
-        e = set_lds_limit<k>(lds_max);
+        e = lds_limit<k>(lds_max);
         return;
       }
     }
     constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, false>;
     kern = k;
-    e = set_lds_limit<k>(lds_max);
+    e = lds_limit<k>(lds_max);
   };
   if constexpr (sizeof(T) == 2) {
     if (path == DIRECT) pick(std::integral_constant<Path, DIRECT>{});

@@ -683,16 +683,6 @@ void wide_pair_kernel(GemmDesc gw, GemmDesc gp, int first, int t1, int n1, int t
   else WP::run(gp, smem, lin, total, 1);
 }
 
-template <auto K>
-hipError_t lds_limit(size_t bytes) {
-  static bool done = false;  // harmless if repeated
-  if (done) return hipSuccess;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(K),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
-  if (e == hipSuccess) done = true;
-  return e;
-}
-
 template <class W>
 int64_t wide_tiles(const GemmDesc& g) {
   return int64_t((g.M + W::BM - 1) / W::BM) * ((g.N + W::BN - 1) / W::BN) *
