@@ -109,9 +109,10 @@ __device__ __forceinline__ bool wide_fault(const CoordMap& mp, int N, const abft
 }
 
 // TC: output type (bf16, or fp32 for the weight gradients); WGM x WGN waves
-// of 128 x 16 JN outputs; NST LDS stages of 64 k each.
-template <class TC, bool AK, bool BKM, int WGM, int WGN, int JN, int NST, bool PROT>
+// of 128 x 16 JN outputs; two LDS stages of 64 k each.
+template <class TC, bool AK, bool BKM, int WGM, int WGN, int JN, bool PROT>
 struct Wide {
+  static constexpr int NST = 2;
   static constexpr int IM = 8, WM = 128, WN = 16 * JN;
   static constexpr int BM = WM * WGM, BN = WN * WGN, NW = WGM * WGN, NTH = 64 * NW;
   using OA = Opnd<AK, BM, NW>;
@@ -225,23 +226,6 @@ struct Wide {
         dma16(rb, lb0 + st + j * 1024, vb, sb[j] + uint32_t(kt) * kb);
       if (sx) dma16(rs, lds_s + st, vs, ss + uint32_t(kt) * 128);
     };
-    // waits until at most `later` whole stages of this wave's copies are in flight
-    auto wait_stage = [&](int later) {
-      if (NST > 3 && later >= 3) {
-        if (sx) wait_vm<3 * (NPER + 1)>();
-        else wait_vm<3 * NPER>();
-      } else if (NST > 2 && later >= 2) {
-        if (sx) wait_vm<2 * (NPER + 1)>();
-        else wait_vm<2 * NPER>();
-      } else if (later >= 1) {
-        if (sx) wait_vm<NPER + 1>();
-        else wait_vm<NPER>();
-      } else {
-        wait_vm<0>();
-      }
-    };
-    static_assert(NST >= 2 && NST <= 4, "stages waited for");
-
     floatx4 acc[IM][JN], accs[JS], accr[IS];
 #pragma unroll
     for (int i = 0; i < IM; ++i)
@@ -319,7 +303,10 @@ struct Wide {
     for (int s = 0; s < NST && s < nk; ++s) issue(s);
     if (nk > 0) {
       Frags f0, f1;
-      wait_stage(nk >= NST ? NST - 1 : 0);
+      // stage 0 has landed; stage 1's copies of this wave are in flight
+      if (nk == 1) wait_vm<0>();
+      else if (sx) wait_vm<NPER + 1>();
+      else wait_vm<NPER>();
       wg_barrier();
       {
         const char* st = smem;
@@ -334,7 +321,7 @@ struct Wide {
       for (int kt = 0; kt < nk; ++kt) {
         phase(f0, f1, smem + cur * STAGE, 1);
         // every read of stage kt is complete; stage kt + 1 has landed
-        wait_stage(min(NST - 2, nk - 2 - kt));
+        wait_vm<0>();
         wg_barrier();
         if (kt + NST < nk) issue(kt + NST);
         cur = cur + 1 == NST ? 0 : cur + 1;
@@ -702,7 +689,7 @@ hipError_t launch_w(const GemmDesc& g, hipStream_t s) {
 // tile with all CUs busy, and per tile besides): 256 x 256 1.75 and 7, one
 // workgroup per CU; 256 x 192 1.4 and 8; 128 x 128 0.58 and 2.3, two
 // workgroups per CU (the 0.58 is per workgroup). Larger tiles ask L2 and LDS
-// for less per flop (28.7, 31.1, 35.4 ps per output and step); smaller ones
+// for less per flop (26.7, 28.5, 35.4 ps per output and step); smaller ones
 // leave fewer CUs idle in the last round. Tiles with one wave per SIMD
 // (128 x 256 or 128 x 192, four waves, three stages) measured half as fast.
 enum { W256 = 0, W192 = 1, W128 = 2, NWIDE = 3 };
@@ -714,13 +701,13 @@ constexpr WideCost COST[NWIDE] = {{256, 256, 1.75, 7.0}, {256, 192, 1.4, 8.0}, {
 constexpr int CUS = 256;
 
 template <class TC, bool AK, bool BKM, bool PROT> struct Shape256 {
-  using T = Wide<TC, AK, BKM, 2, 4, 4, 2, PROT>;
+  using T = Wide<TC, AK, BKM, 2, 4, 4, PROT>;
 };
 template <class TC, bool AK, bool BKM, bool PROT> struct Shape192 {
-  using T = Wide<TC, AK, BKM, 2, 4, 3, 2, PROT>;
+  using T = Wide<TC, AK, BKM, 2, 4, 3, PROT>;
 };
 template <class TC, bool AK, bool BKM, bool PROT> struct Shape128 {
-  using T = Wide<TC, AK, BKM, 1, 4, 2, 2, PROT>;
+  using T = Wide<TC, AK, BKM, 1, 4, 2, PROT>;
 };
 
 bool has_checks(const GemmDesc& g) { return g.Ac != nullptr || g.Br != nullptr || g.verify != 0; }
@@ -770,7 +757,10 @@ bool wide_operands_ok(const GemmDesc& g, bool c_fp32, bool ak, bool bk) {
       return false;
   }
   if (g.splitk > 1 && !c_fp32) return false;
-  return true;
+  // the kernel shifts by the block sizes and writes no images of its output's
+  // checksums
+  auto pow2 = [](int x) { return x > 0 && (x & (x - 1)) == 0; };
+  return pow2(g.Rm) && pow2(g.Rn) && g.Cci == nullptr && g.Cri == nullptr;
 }
 
 template <template <class, bool, bool, bool> class S>
