@@ -61,9 +61,9 @@ struct Layout_ {
   size_t total;
 };
 
-// K slices for a weight-gradient GEMM (M x N tiles of 128 x 128, long K):
-// enough slices to give at least 256 workgroups, each slice at least 256
-// deep.
+// K slices for a weight-gradient GEMM, counted in 128 x 128 tiles whatever
+// tile then runs them (the workspace is sized by this count): enough slices
+// to give at least 256 workgroups, each slice at least 256 deep.
 int splitk_for(int64_t M, int64_t N, int64_t K, bool prot) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
   int ks = 1;
@@ -278,8 +278,8 @@ Params make_params(const attn_abft_config* c, const Dims& d) {
   return p;
 }
 
-// Projection tile: 128 x 128 (two workgroups per CU with the direct
-// operand path); a 256 x 128 tile fits one per CU and measured slower.
+// Projection tile where the wide tiles do not take the product (fp32 widths
+// are chosen at the launch).
 Tile proj_tile() { return Tile::T128x128; }
 
 #define CK(x)                                          \

@@ -1656,7 +1656,11 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
 
 // Columns of an fp32 tile (128 rows): the width at which the CUs' rounds of
 // tiles cost least, a narrower tile paying for reading A more often. A row
-// checksum block lies in one tile.
+// checksum block lies in one tile. Measured per column with every CU busy
+// (T 4096 H 2048, us at 128 / 64 / 32 columns): out 391 / 411 / 554, dV 247 /
+// 264 / 339, dX 1041 / 1050 / 1300, dWqkv 1276 / 1347 / 1855; unprotected out
+// 307 / 349 / 412. With few tiles the narrow ones win by their rounds: B2 S512
+// H768 dX 197 / 116 / 76.
 int f32_columns(const GemmDesc& g, int most) {
   int best = most;
   double t = -1;
@@ -1665,7 +1669,7 @@ int f32_columns(const GemmDesc& g, int most) {
     if (g.Br != nullptr && (g.Rn > bn || g.cr_n_begin % bn != 0)) break;
     const int64_t tiles = int64_t((g.M + 127) / 128) * ((g.N + bn - 1) / bn) * g.nb0 * g.nb1 *
                           (g.splitk > 1 ? g.splitk : 1);
-    const double c = double((tiles + 255) / 256) * bn * (bn == 128 ? 1.0 : bn == 64 ? 1.1 : 1.25);
+    const double c = double((tiles + 255) / 256) * bn * (bn == 128 ? 1.0 : bn == 64 ? 1.1 : 1.4);
     if (t < 0 || c < t) { t = c; best = bn; }
   }
   return best;
