@@ -115,10 +115,10 @@ KERNEL_OF_STAGE = {
     "core_kv": ("fused_bwd_kv_kernel<64, true, 0>", 768),
     "core_q": ("fused_bwd_q_kernel<64, true>", 768),
     "attn": ("fused_attn_kernel<64, true>", 768),
-    "qkv": ("gemm_kernel<unsigned short, unsigned short, true, false, 128, 128, true, 2, true, true>", 1152),
-    "softmax_bwd": ("softmax_kernel<unsigned short, 2, true, 1, true, true>", 768),
-    "softmax": ("softmax_kernel<unsigned short, 2, false, 1, true, true>", 768),
-    "score": ("gemm_kernel<unsigned short, unsigned short, true, true, 128, 128, true, 1, true, true>", 3456),
+    "qkv": ("wide_kernel<Wide<unsigned short, true, false, 1, 4, 2, true> >", 1152),
+    "softmax_bwd": ("softmax_kernel<unsigned short, 2, true, 1, true, true, 4, false>", 768),
+    "softmax": ("softmax_kernel<unsigned short, 2, false, 1, true, true, 4, false>", 768),
+    "score": ("gemm_kernel<unsigned short, unsigned short, true, true, 128, 128, true, 1, 1, true>", 3456),
 }
 
 
@@ -128,6 +128,9 @@ _COMMON_SOURCES = ("paper_2410_11720_amd/csrc/abft_device.hpp",
                    "paper_2410_11720_amd/csrc/abft_internal.hpp", "include/attn_abft.h")
 KERNEL_SOURCES = {
     "gemm_kernel": ("paper_2410_11720_amd/csrc/gemm_abft.hip",
+                    "paper_2410_11720_amd/csrc/direct_lds.hpp") + _COMMON_SOURCES,
+    "wide_kernel": ("paper_2410_11720_amd/csrc/gemm_wide.hip",
+                    "paper_2410_11720_amd/csrc/wide_copy.hpp",
                     "paper_2410_11720_amd/csrc/direct_lds.hpp") + _COMMON_SOURCES,
     "softmax_kernel": ("paper_2410_11720_amd/csrc/softmax_abft.hip",) + _COMMON_SOURCES,
     "fused_attn_kernel": ("paper_2410_11720_amd/csrc/fused_attn.hip",

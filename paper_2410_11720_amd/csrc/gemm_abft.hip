@@ -31,8 +31,10 @@ namespace {
 // takes 32 cycles for 2048 flop, so LDS and L2 keep up with small tiles, but a
 // protected 128 x 128 fp32 tile fills more than half the LDS: with four waves
 // that was one per SIMD, each waiting out its own LDS latency and barriers
-// (T 4096 H 2048 fp32 QKV 1535 -> 1250 us; unprotected, where two workgroups
-// of four waves fit, the same within 3%).
+// (T 4096 H 2048 fp32 QKV 1560 -> 1245 us). Unprotected, where two workgroups
+// of four waves fit, the largest projections pay for it (QKV 870 -> 907 us,
+// dX 823 -> 854; four waves alone 886 and 856) and all else gains: the step
+// 5536 -> 5140, B8 S512 H768 1101 -> 983.
 template <class T>
 constexpr int threads_of() {
   return sizeof(T) == 4 ? 512 : 256;
@@ -1570,9 +1572,9 @@ constexpr int gemm_waves_per_eu() {
 }
 
 // Operand paths: through registers, direct to LDS, direct with a half stage.
-enum Path { REGS = 0, DIRECT = 1, DIRECT_HALF = 2 };
+constexpr int REGS = 0, DIRECT = 1, DIRECT_HALF = 2;
 
-template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, Path P,
+template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, int P,
           bool WLC>
 __global__ __launch_bounds__(threads_of<T>()) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && P != REGS>())))
 void gemm_kernel(GemmDesc g) {
@@ -1587,7 +1589,7 @@ void gemm_kernel(GemmDesc g) {
 // M or N extent of an MN-major operand. A one-stage tile takes whole stages
 // only (its K is a head dim).
 template <class T>
-Path path_of(const GemmDesc& g, bool ak, bool bk, int nstage) {
+int path_of(const GemmDesc& g, bool ak, bool bk, int nstage) {
   if (sizeof(T) != 2 || g.K % (nstage == 1 ? 64 : 32) != 0) return REGS;
   auto al = [](const void* p, int64_t ld, int64_t s0, int64_t s1) {
     return reinterpret_cast<uintptr_t>(p) % 16 == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
@@ -1603,7 +1605,7 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   using G = Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE>;
   if (G::COLS_ONLY && (g.Br != nullptr || g.verify == 2)) return hipErrorInvalidValue;
   const bool gcc = PROT && g.Ac != nullptr, gcr = PROT && g.Br != nullptr;
-  const Path path = path_of<T>(g, AK, BKM, NSTAGE);
+  const int path = path_of<T>(g, AK, BKM, NSTAGE);
   const size_t main = path != REGS ? G::d_main_bytes(gcc, gcr) : G::main_bytes(gcc, gcr);
   // split-K slices skip the staged epilogue: only the operand stages (and
   // the 16 x BN checksum strip image inside them) are needed
@@ -1622,7 +1624,7 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   auto kern = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, REGS, false>;
   hipError_t e = hipSuccess;
   auto pick = [&](auto p) {
-    constexpr Path P = decltype(p)::value;
+    constexpr int P = decltype(p)::value;
     if constexpr (G::MSUM) {
       if (wlc) {
         constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, true>;
@@ -1636,11 +1638,11 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
     e = lds_limit<k>(lds_max);
   };
   if constexpr (sizeof(T) == 2) {
-    if (path == DIRECT) pick(std::integral_constant<Path, DIRECT>{});
+    if (path == DIRECT) pick(std::integral_constant<int, DIRECT>{});
     if constexpr (NSTAGE > 1)
-      if (path == DIRECT_HALF) pick(std::integral_constant<Path, DIRECT_HALF>{});
+      if (path == DIRECT_HALF) pick(std::integral_constant<int, DIRECT_HALF>{});
   }
-  if (path == REGS) pick(std::integral_constant<Path, REGS>{});
+  if (path == REGS) pick(std::integral_constant<int, REGS>{});
   if (e != hipSuccess) return e;
   const int64_t ntm = (g.M + BM - 1) / BM, ntn = (g.N + BN - 1) / BN;
   const int64_t tiles = tri_tiles(g, BM, BN) ? ntm * (ntm + 1) / 2 : ntm * ntn;
