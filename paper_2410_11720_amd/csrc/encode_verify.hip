@@ -617,12 +617,14 @@ hipError_t verify_t(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld,
 // The chunked detection takes what the encoder's vector path takes (aligned
 // rows, row blocks of a power of two of at most 16 chunks); slabs of 8
 // chunks, 16 where a row block needs them (32 would be slower: the sums over
-// 32 lanes, 8 x 128 x 128 fp32 24.1 us against 21.5). Any other shape, and one
+// 32 lanes, 8 x 128 x 128 fp32 24.1 us against 19.4). Any other shape, and one
 // whose correction's counters would not fit beside the detection's LDS: one
-// thread per vector, over slabs of about 256 columns while the row blocks
-// alone do not fill the chip (8 x 1024 x 768 fp32, 64 row blocks, 58 -> 38 us
-// as slabs; 8 x 700 x 900 in blocks of 7, 800 of them, 73 -> 77). Where the
-// slabs do not fit the grid, a workgroup takes whole rows.
+// thread per vector, over slabs of about 128 columns (half the waves take
+// columns, half row vectors) while the row blocks alone do not fill the chip
+// (8 x 1024 x 768 fp32, 64 row blocks, 56 -> 34 us as slabs; 3 x 256 x 256
+// 27.7 -> 24.5, 27.8 with slabs of 256; 8 x 700 x 900 in blocks of 7, 800 of
+// them, 73 -> 77 as slabs). Where the slabs do not fit the grid, a workgroup
+// takes whole rows.
 template <class T>
 hipError_t verify_d(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld, int64_t bs, int Rb,
                     int Cb, float* col_chk, float* row_chk, float tn, float tc, float e_rel,
@@ -639,7 +641,7 @@ hipError_t verify_d(T* C, int64_t batch, int64_t rows, int64_t cols, int64_t ld,
   const int64_t counters = row_chk != nullptr ? Rb * (slab / Cb) + slab : 0;
   fast = fast && counters <= 128 * 1024 / 4;
   if (!fast) {
-    slab = row_chk != nullptr ? (255 / Cb + 1) * int64_t(Cb) : 256;
+    slab = row_chk != nullptr ? (127 / Cb + 1) * int64_t(Cb) : 256;
     if (slab > cols || rows / Rb * batch >= 512) slab = cols;
   }
   if ((cols + slab - 1) / slab > 0xffff) {
