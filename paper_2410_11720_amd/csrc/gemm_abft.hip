@@ -31,13 +31,11 @@ namespace {
 // takes 32 cycles for 2048 flop, so LDS and L2 keep up with small tiles, but a
 // protected 128 x 128 fp32 tile fills more than half the LDS: with four waves
 // that was one per SIMD, each waiting out its own LDS latency and barriers
-// (T 4096 H 2048 fp32 QKV 1560 -> 1245 us). Unprotected, where two workgroups
-// of four waves fit, the largest projections pay for it (QKV 870 -> 907 us,
-// dX 823 -> 854; four waves alone 886 and 856) and all else gains: the step
-// 5536 -> 5140, B8 S512 H768 1101 -> 983.
-template <class T>
+// (T 4096 H 2048 fp32 QKV 1560 -> 1245 us). NARROW: four waves after all, with
+// 4-byte fragments, for unprotected tiles (see launch_tile).
+template <class T, bool NARROW>
 constexpr int threads_of() {
-  return sizeof(T) == 4 ? 512 : 256;
+  return sizeof(T) == 4 && !NARROW ? 512 : 256;
 }
 
 // The kernel's descriptor (argument `slot` of the kernel: the descriptors
@@ -81,6 +79,18 @@ template <> struct Mfma<float> {
 #pragma unroll
     for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
     return c;
+  }
+};
+// The same with one k per lane and MFMA: four times the LDS reads, a quarter
+// of the fragment registers.
+struct MfmaNarrow {
+  static constexpr int BK = 32;
+  static constexpr int KI = 4;
+  static constexpr int PAD = 4;
+  typedef float frag;
+  __device__ static frag load(const float* p) { return *p; }
+  __device__ static floatx4 mma(frag a, frag b, floatx4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
 };
 
@@ -395,12 +405,13 @@ __device__ __forceinline__ TileIdx tile_of(const GemmDesc& g, int lin, int total
 // without a workgroup barrier (outputs checked on the column side only).
 // Otherwise the waves form a 2 x 2 grid.
 template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE,
-          bool WLC = false>
+          bool WLC = false, bool NARROW = false>
 struct Gemm {
-  static constexpr int NT = threads_of<T>();
-  static constexpr int BK = Mfma<T>::BK;
-  static constexpr int KI = Mfma<T>::KI;
-  static constexpr int LDK = BK + Mfma<T>::PAD;
+  static constexpr int NT = threads_of<T, NARROW>();
+  using MF = std::conditional_t<NARROW, MfmaNarrow, Mfma<T>>;
+  static constexpr int BK = MF::BK;
+  static constexpr int KI = MF::KI;
+  static constexpr int LDK = BK + MF::PAD;
   static constexpr int WGN = WLC ? 4 : 2, WGM = NT / 64 / WGN;  // wave grid
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int IM = WM / 16, JN = WN / 16;
@@ -553,7 +564,7 @@ struct Gemm {
     // tile's fragments so that one wait covers them all (a GEMM without a
     // column strip reads the stage's first rows instead: a valid address,
     // the value unused)
-    using Frag = typename Mfma<T>::frag;
+    using Frag = typename MF::frag;
     // the column strip copied from its bf16 image (direct path): 2 nc rows
     // of 64 elements, unpadded; fragment rows past them repeat the rows
     // (their MFMA result rows are not read)
@@ -575,8 +586,8 @@ struct Gemm {
     const int wmu = __builtin_amdgcn_readfirstlane(wm), wnu = __builtin_amdgcn_readfirstlane(wn);
     auto strip_frags = [&](const T* st0, const T* sS, const T* sR, int kk, Frag& sf, Frag& rf) {
       if (PROT && EARLY) {
-        sf = Mfma<T>::load((cc ? sS + soff : st0 + fr * LDK + fk) + kk);
-        if (cr) rf = Mfma<T>::load(sR + roff + kk);
+        sf = MF::load((cc ? sS + soff : st0 + fr * LDK + fk) + kk);
+        if (cr) rf = MF::load(sR + roff + kk);
       }
     };
     // the MFMAs of one KI-wide k step: the tile, then the checksum strips
@@ -585,26 +596,26 @@ struct Gemm {
 #pragma unroll
       for (int i = 0; i < IM; ++i)
 #pragma unroll
-        for (int j = 0; j < JN; ++j) acc[i][j] = Mfma<T>::mma(af[i], bfr[j], acc[i][j]);
+        for (int j = 0; j < JN; ++j) acc[i][j] = MF::mma(af[i], bfr[j], acc[i][j]);
       if (PROT && !EARLY) {
         if (cc) {
-          const auto sfl = Mfma<T>::load(sS + fr * LDK + kk + fk);
+          const auto sfl = MF::load(sS + fr * LDK + kk + fk);
 #pragma unroll
           for (int j = 0; j < JS; ++j) {
             auto bsel = bfr[j];
 #pragma unroll
             for (int w = 1; w < WGM; ++w) bsel = wm == w ? bfr[min(w * JS + j, JN - 1)] : bsel;
-            accs[j] = Mfma<T>::mma(sfl, bsel, accs[j]);
+            accs[j] = MF::mma(sfl, bsel, accs[j]);
           }
         }
         if (cr) {
-          const auto rfl = Mfma<T>::load(sR + fr * LDK + kk + fk);
+          const auto rfl = MF::load(sR + fr * LDK + kk + fk);
 #pragma unroll
           for (int i = 0; i < IS; ++i) {
             auto asel = af[i];
 #pragma unroll
             for (int w = 1; w < WGN; ++w) asel = wn == w ? af[min(IS * w + i, IM - 1)] : asel;
-            accr[i] = Mfma<T>::mma(rfl, asel, accr[i]);
+            accr[i] = MF::mma(rfl, asel, accr[i]);
           }
         }
       }
@@ -615,7 +626,7 @@ struct Gemm {
             if (wmu == w) {
 #pragma unroll
               for (int j = 0; j < JS; ++j)
-                if (w * JS + j < JN) accs[j] = Mfma<T>::mma(sf, bfr[w * JS + j], accs[j]);
+                if (w * JS + j < JN) accs[j] = MF::mma(sf, bfr[w * JS + j], accs[j]);
             }
         }
         if (cr) {
@@ -624,7 +635,7 @@ struct Gemm {
             if (wnu == w) {
 #pragma unroll
               for (int i = 0; i < IS; ++i)
-                if (IS * w + i < IM) accr[i] = Mfma<T>::mma(rf, af[IS * w + i], accr[i]);
+                if (IS * w + i < IM) accr[i] = MF::mma(rf, af[IS * w + i], accr[i]);
             }
         }
       }
@@ -700,7 +711,7 @@ struct Gemm {
 #pragma unroll
           for (int kk = 0; kk < BK; kk += KI) {
             if (HALF && kk >= kleft) break;  // (half stage: its second half is not there)
-            typename Mfma<T>::frag af[IM], bfr[JN];
+            typename MF::frag af[IM], bfr[JN];
             // MN-major images are read with transposing reads that are
             // waited for together
             TrPair ap[AK ? 1 : IM], bp[BKM ? 1 : JN];
@@ -797,13 +808,13 @@ struct Gemm {
       const T* sR = sS + r_off;
 #pragma unroll
       for (int kk = 0; kk < BK; kk += KI) {
-        typename Mfma<T>::frag af[IM], bfr[JN];
+        typename MF::frag af[IM], bfr[JN];
 #pragma unroll
         for (int i = 0; i < IM; ++i)
-          af[i] = Mfma<T>::load(sA + (wm * WM + i * 16 + fr) * LDK + kk + fk);
+          af[i] = MF::load(sA + (wm * WM + i * 16 + fr) * LDK + kk + fk);
 #pragma unroll
         for (int j = 0; j < JN; ++j)
-          bfr[j] = Mfma<T>::load(sB + (wn * WN + j * 16 + fr) * LDK + kk + fk);
+          bfr[j] = MF::load(sB + (wn * WN + j * 16 + fr) * LDK + kk + fk);
         Frag sf, rf;
         strip_frags(sA, sS, sR, kk, sf, rf);
         mma_kk(af, bfr, sf, rf, sS, sR, kk);
@@ -1015,8 +1026,8 @@ struct Gemm {
                                pk[2 * sg + 1][j][1]};
               const uint4 ua = {u.x & 0x7fff7fffu, u.y & 0x7fff7fffu, u.z & 0x7fff7fffu,
                                 u.w & 0x7fff7fffu};
-              const floatx4 sm = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
-              const floatx4 mg = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
+              const floatx4 sm = MF::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
+              const floatx4 mg = MF::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
               if (lane < 16)
                 reinterpret_cast<float2*>(colp)[(wm * (WM / SEG) + sg) * BN + wn * WN + j * 16 +
                                                 lane] = float2{sm[0], mg[0]};
@@ -1036,8 +1047,8 @@ struct Gemm {
                 tile + (r0 + (lane & 15)) * LDT + sg * SEG + 8 * (lane >> 4));
             const uint4 ua = {u.x & 0x7fff7fffu, u.y & 0x7fff7fffu, u.z & 0x7fff7fffu,
                               u.w & 0x7fff7fffu};
-            const floatx4 sm = Mfma<T>::mma(__builtin_bit_cast(bf16x8, u), ones, zero);
-            const floatx4 mg = Mfma<T>::mma(__builtin_bit_cast(bf16x8, ua), ones, zero);
+            const floatx4 sm = MF::mma(__builtin_bit_cast(bf16x8, u), ones, zero);
+            const floatx4 mg = MF::mma(__builtin_bit_cast(bf16x8, ua), ones, zero);
             if ((lane & 15) == 0) {
               float4* o = reinterpret_cast<float4*>(rowp + (sg * BM + r0 + 4 * (lane >> 4)) * 2);
               o[0] = float4{sm[0], mg[0], sm[1], mg[1]};
@@ -1218,8 +1229,8 @@ struct Gemm {
                            pk[2 * sg + 1][j][1]};
           const uint4 ua = {u.x & 0x7fff7fffu, u.y & 0x7fff7fffu, u.z & 0x7fff7fffu,
                             u.w & 0x7fff7fffu};
-          const floatx4 sm = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
-          const floatx4 mg = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
+          const floatx4 sm = MF::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
+          const floatx4 mg = MF::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
           if (((sg * SEG) >> lg_rm) == g4) {
             r1 += sm[0];
             sa += mg[0];
@@ -1266,8 +1277,8 @@ struct Gemm {
         if (nrb > 0) {
           const uint4 ua = {u.x & 0x7fff7fffu, u.y & 0x7fff7fffu, u.z & 0x7fff7fffu,
                             u.w & 0x7fff7fffu};
-          const floatx4 sm = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
-          const floatx4 mg = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
+          const floatx4 sm = MF::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
+          const floatx4 mg = MF::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
           if (g4 == 0) part[wn * BM + i * 16 + fr] = float2{sm[0], mg[0]};
         }
       }
@@ -1330,8 +1341,8 @@ struct Gemm {
                   tile + (i * 16 + fr) * LDT + wn * WN + t * SEG + 8 * g4);
               const uint4 ua = {u.x & 0x7fff7fffu, u.y & 0x7fff7fffu, u.z & 0x7fff7fffu,
                                 u.w & 0x7fff7fffu};
-              const floatx4 sm = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
-              const floatx4 mg = Mfma<T>::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
+              const floatx4 sm = MF::mma(ones, __builtin_bit_cast(bf16x8, u), zero);
+              const floatx4 mg = MF::mma(ones, __builtin_bit_cast(bf16x8, ua), zero);
               if (g4 == 0) part[(wn * TS + t) * BM + i * 16 + fr] = float2{sm[0], mg[0]};
             }
         }
@@ -1565,9 +1576,9 @@ struct Gemm {
 // the direct path (a few spills, far cheaper than the lost workgroup).
 // fp32 tiles of 128 x 64 or less, and the weight gradients (whose K slices
 // need the operand stages only): two workgroups of eight waves.
-template <class T, bool WGRAD, int BM, int BN, bool PROT, int NSTAGE, bool WLC>
+template <class T, bool WGRAD, int BM, int BN, bool PROT, int NSTAGE, bool WLC, bool NARROW>
 constexpr int gemm_waves_per_eu() {
-  if (sizeof(T) == 4) return BN <= 64 || WGRAD ? 4 : 2;
+  if (sizeof(T) == 4 && !NARROW) return BN <= 64 || WGRAD ? 4 : 2;
   return BM * BN > 128 * 128 ? 1 : (sizeof(T) == 2 && NSTAGE == 1 && (!PROT || WLC) ? 3 : 2);
 }
 
@@ -1575,11 +1586,11 @@ constexpr int gemm_waves_per_eu() {
 constexpr int REGS = 0, DIRECT = 1, DIRECT_HALF = 2;
 
 template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE, int P,
-          bool WLC>
-__global__ __launch_bounds__(threads_of<T>()) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && P != REGS>())))
+          bool WLC, bool NARROW>
+__global__ __launch_bounds__((threads_of<T, NARROW>())) __attribute__((amdgpu_waves_per_eu(gemm_waves_per_eu<T, !AK && !BKM, BM, BN, PROT, NSTAGE, WLC && P != REGS, NARROW>())))
 void gemm_kernel(GemmDesc g) {
   extern __shared__ __align__(16) char smem[];
-  Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, WLC>::template run<P != REGS, P == DIRECT_HALF>(
+  Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, WLC, NARROW>::template run<P != REGS, P == DIRECT_HALF>(
       g, smem, blockIdx.x, gridDim.x, 0);
 }
 
@@ -1600,9 +1611,10 @@ int path_of(const GemmDesc& g, bool ak, bool bk, int nstage) {
   return g.K % 64 != 0 ? DIRECT_HALF : DIRECT;
 }
 
-template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE = 2>
+template <class T, class TC, bool AK, bool BKM, int BM, int BN, bool PROT, int NSTAGE = 2,
+          bool NARROW = false>
 hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
-  using G = Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE>;
+  using G = Gemm<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, false, NARROW>;
   if (G::COLS_ONLY && (g.Br != nullptr || g.verify == 2)) return hipErrorInvalidValue;
   const bool gcc = PROT && g.Ac != nullptr, gcr = PROT && g.Br != nullptr;
   const int path = path_of<T>(g, AK, BKM, NSTAGE);
@@ -1621,19 +1633,19 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
   // segments)
   if constexpr (G::MSUM)
     wlc = g.splitk <= 1 && (g.verify <= 1 || BN / 4 >= 32) && (g.Ac == nullptr || g.Rm <= BM);
-  auto kern = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, REGS, false>;
+  auto kern = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, REGS, false, NARROW>;
   hipError_t e = hipSuccess;
   auto pick = [&](auto p) {
     constexpr int P = decltype(p)::value;
     if constexpr (G::MSUM) {
       if (wlc) {
-        constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, true>;
+        constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, true, NARROW>;
         kern = k;
         e = lds_limit<k>(lds_max);
         return;
       }
     }
-    constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, false>;
+    constexpr auto k = gemm_kernel<T, TC, AK, BKM, BM, BN, PROT, NSTAGE, P, false, NARROW>;
     kern = k;
     e = lds_limit<k>(lds_max);
   };
@@ -1663,15 +1675,17 @@ hipError_t launch_t(const GemmDesc& g, hipStream_t s) {
 // 264 / 339, dX 1041 / 1050 / 1300, dWqkv 1276 / 1347 / 1855; unprotected out
 // 307 / 349 / 412. With few tiles the narrow ones win by their rounds: B2 S512
 // H768 dX 197 / 116 / 76.
+int64_t f32_tiles(const GemmDesc& g, int bn) {
+  return int64_t((g.M + 127) / 128) * ((g.N + bn - 1) / bn) * g.nb0 * g.nb1 *
+         (g.splitk > 1 ? g.splitk : 1);
+}
 int f32_columns(const GemmDesc& g, int most) {
   int best = most;
   double t = -1;
   for (int bn = most; bn >= 32; bn /= 2) {
     if (g.verify == 2 && g.Rn > bn) break;
     if (g.Br != nullptr && (g.Rn > bn || g.cr_n_begin % bn != 0)) break;
-    const int64_t tiles = int64_t((g.M + 127) / 128) * ((g.N + bn - 1) / bn) * g.nb0 * g.nb1 *
-                          (g.splitk > 1 ? g.splitk : 1);
-    const double c = double((tiles + 255) / 256) * bn * (bn == 128 ? 1.0 : bn == 64 ? 1.1 : 1.4);
+    const double c = double((f32_tiles(g, bn) + 255) / 256) * bn * (bn == 128 ? 1.0 : bn == 64 ? 1.1 : 1.4);
     if (t < 0 || c < t) { t = c; best = bn; }
   }
   return best;
@@ -1690,10 +1704,18 @@ hipError_t launch_tile(const GemmDesc& g, Tile tile, hipStream_t s) {
     if constexpr (AK && BKM)
       if (tile == Tile::T128x128S1) return launch_t<T, TC, AK, BKM, 128, 128, PROT, 1>(g, s);
     if constexpr (sizeof(T) == 4) {
-      switch (f32_columns(g, tile == Tile::T128x64 ? 64 : 128)) {
-        case 32: return launch_t<T, TC, AK, BKM, 128, 32, PROT>(g, s);
-        case 64: return launch_t<T, TC, AK, BKM, 128, 64, PROT>(g, s);
-      }
+      const int bn = f32_columns(g, tile == Tile::T128x64 ? 64 : 128);
+      // Unprotected, two workgroups of four waves share a CU, and with tiles
+      // enough for both the narrow form is the faster one: T 4096 H 2048 QKV
+      // 907 -> 866 us, out 309 -> 293, dX 860 -> 828 (192 tiles: dX of T 4096
+      // H 768 165 -> 176). Not for the weight gradients (875 -> 1190).
+      const bool many = !PROT && f32_tiles(g, bn) > 256;
+      if constexpr (!PROT && AK)
+        if (bn == 128 && many) return launch_t<T, TC, AK, BKM, 128, 128, PROT, 2, true>(g, s);
+      if constexpr (!PROT)
+        if (bn == 64 && many) return launch_t<T, TC, AK, BKM, 128, 64, PROT, 2, true>(g, s);
+      if (bn == 32) return launch_t<T, TC, AK, BKM, 128, 32, PROT>(g, s);
+      if (bn == 64) return launch_t<T, TC, AK, BKM, 128, 64, PROT>(g, s);
       return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
     } else {
       if (tile == Tile::T128x128) return launch_t<T, TC, AK, BKM, 128, 128, PROT>(g, s);
