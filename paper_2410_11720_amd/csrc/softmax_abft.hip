@@ -525,7 +525,10 @@ hipError_t launch_waves(const SoftmaxDesc& d, bool chk, unsigned grid, hipStream
 // over more waves, as many as keep the whole grid resident (128 registers a
 // lane: 16 waves per CU; the waves' column slabs in LDS): B2 S512 12 heads
 // fp32, 96 workgroups, 48 us with 4 waves, 22 with 16. A full grid
-// measured no faster with 8 waves than with 4.
+// measured no faster with 8 waves than with 4, nor does the unchecked
+// backward at two workgroups a CU, bound by its three tensors: B6 S1024 8x64
+// unmasked 51.8 us with 4, 55.4 with 8 (the unchecked forward, two tensors,
+// 27.4 and 24.6).
 template <class T, int CH, bool BWD>
 hipError_t launch_ch(const SoftmaxDesc& d, bool chk, hipStream_t s) {
   const unsigned grid = unsigned((d.S / d.R) * d.B * d.nh);
@@ -536,7 +539,7 @@ hipError_t launch_ch(const SoftmaxDesc& d, bool chk, hipStream_t s) {
              size_t(d.S) * 2 * nw * sizeof(float) * per_cu <= 144 * 1024;
     };
     if (fits(16, 1)) return launch_waves<T, CH, BWD, 16>(d, chk, grid, s);
-    if (fits(8, 2)) return launch_waves<T, CH, BWD, 8>(d, chk, grid, s);
+    if ((chk || !BWD) && fits(8, 2)) return launch_waves<T, CH, BWD, 8>(d, chk, grid, s);
   }
   // The longest rows of the forward (S > 2048 bf16): a column slab per wave
   // is 128 KB at 4096 keys, one workgroup per CU. One slab, added to in turn,
