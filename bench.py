@@ -118,7 +118,7 @@ KERNEL_OF_STAGE = {
     "qkv": ("wide_kernel<Wide<unsigned short, true, false, 1, 4, 2, true> >", 1152),
     "softmax_bwd": ("softmax_kernel<unsigned short, 2, true, 1, true, true, 4, false>", 768),
     "softmax": ("softmax_kernel<unsigned short, 2, false, 1, true, true, 4, false>", 768),
-    "score": ("gemm_kernel<unsigned short, unsigned short, true, true, 128, 128, true, 1, 1, true>", 3456),
+    "score": ("gemm_kernel<unsigned short, unsigned short, true, true, 128, 128, true, 1, 1, true, false>", 3456),
 }
 
 
